@@ -231,6 +231,11 @@ void bn_relu_bwd(Ctx &cx, View x, const float *da, int c, Geo g, const float *st
 void conv_fwd(Ctx &cx, View x, const float *scale_shift, rvn_dtype dt, const float *w, const uint16_t *wq, int cin,
               int cout, int ks, Geo g, Epilogue ep, const View *r, View out, float *scratch);
 
+// The same convolution with fp32 operands as a tiled matrix product over the flat pixel index
+// (conv_gemm_f32.hip); returns false (nothing launched) for the shapes it does not take.
+bool conv_gemm_f32(Ctx &cx, View in, const float *scale_shift, const float *w, bool transposed, int ci, int co, int ks,
+                   Geo g, Epilogue ep, const View *r, View out);
+
 // The same convolution on bf16 matrix instructions (operands rounded to bf16,
 // fp32 accumulation); `transposed`: w is [ci][co][ks][ks] and is read transposed
 // and flipped (data gradient).  Returns false if no tiling fits (nothing is

@@ -1,0 +1,63 @@
+"""The fp32 convolution and filter gradient over flat pixels, at the sizes where their tiles, channel
+chunks, pixel chunks and staged runs end: against the oracle in float64, one block.  The bars are those of
+the fp32 parity cases (forward 1e-5, gradients 1e-4).  About one ReLU argument in a million lies within
+rounding of zero, and a decision taken the other way changes a gradient tensor of N elements by about
+1 / sqrt(N) of its norm: the case of 2.3 million decisions per layer is held to four of them (4 / 1500 = 2.7e-3)
+where such a decision enters, and to 1e-4 for the median image."""
+import numpy as np
+import pytest
+
+import synth_inputs as S
+from oracle import revnet_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # 17 channels: the fewest taken; one pixel per image short of / past a 32-pixel tile and a 64-pixel chunk
+    dict(kind="basic", n=3, c=34, h=3, w=7),
+    dict(kind="basic", n=1, c=66, h=5, w=13),       # 33 channels, 65 pixels
+    dict(kind="basic", n=1, c=66, h=7, w=9),        # 63 pixels
+    dict(kind="basic", n=1, c=70, h=2, w=63),       # widest rows of the 128-pixel tile; 35 channels
+    dict(kind="basic", n=1, c=80, h=2, w=111),      # widest rows of the 32-pixel tile; no backward plan: forward only
+    dict(kind="basic", n=1, c=68, h=3, w=1),        # one column: every side tap leaves the image
+    dict(kind="bottleneck", n=5, c=136, h=7, w=7, width=33),      # one channel past a 32-channel chunk
+    dict(kind="bottleneck", n=16, c=384, h=14, w=14, width=40),   # several tiles of channels, chunks and slices
+    dict(kind="bottleneck", n=40, c=256, h=28, w=28, width=72),   # large tiles, ragged channels
+    dict(kind="bottleneck", n=2, c=1100, h=7, w=5, width=520),    # filters larger than the activations
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda k: "%s n%d c%d %dx%d" % (k["kind"], k["n"], k["c"], k["h"], k["w"]))
+def test_block_against_oracle(case):
+    import torch
+    from paper_1707_04585_amd.torch_harness import StackRunner, download_grads
+    cfg = dict(width=None, depth=1, conv="f32", affine="random")
+    cfg.update(case)
+    x, params, dy = S.draw_stack(S.BASE_SEED + 909, **cfg)
+    c = cfg["c"] // 2
+    print(case, flush=True)
+    r = StackRunner(**cfg)
+    r.set_params(params)
+    Y, DY = r.new_pair(x), r.new_pair(dy)
+    r.forward(Y, Y)
+    torch.cuda.synchronize()
+    y = r.to_host(Y[0])
+    sp = lambda t: (np.ascontiguousarray(t[:, :c]), np.ascontiguousarray(t[:, c:]))
+    y1, y2, _, stored = O.stack_fwd(*sp(x), params, keep=True)
+    assert O.rel_l2(y, np.concatenate([y1, y2], 1)) < 1e-5
+    if cfg["w"] > 95:
+        return
+    r.backward(Y, DY, Y, DY)
+    torch.cuda.synchronize()
+    x_rec, dx, grads = r.to_host(Y[0]), r.to_host(DY[0]), download_grads(r.grads)
+    dx1, dx2, ref = O.stack_bwd_stored(stored, params, *sp(dy))
+    want_dx = np.concatenate([dx1, dx2], 1)
+    errs = dict(dx=O.rel_l2(dx, want_dx))
+    for fn in ("F", "G"):
+        for l, (got, want) in enumerate(zip(grads[0][fn], ref[0][fn])):
+            errs["%s%d.w" % (fn, l)] = O.rel_l2(got["w"], want["w"])
+    print({k: "%.1e" % v for k, v in errs.items()}, flush=True)
+    assert O.rel_l2(x_rec, x) < 1e-5
+    decisions = cfg["n"] * cfg["h"] * cfg["w"] * (cfg["width"] or c)
+    assert max(errs.values()) < (1e-4 if decisions < 1000000 else 4.0 / decisions ** 0.5), errs
+    assert np.median([O.rel_l2(a, b) for a, b in zip(dx, want_dx)]) < 1e-4
