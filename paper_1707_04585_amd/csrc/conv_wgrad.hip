@@ -21,6 +21,8 @@
 // before the matrix instructions of the current one and land in LDS after
 // them.  The workgroups' partial results are summed by a second kernel in a
 // fixed order (no floating-point atomics: results are bitwise reproducible).
+#include <algorithm>
+
 #include "conv_wgrad_body.h"
 #include "kernels.h"
 #include "wgrad_reduce.h"
@@ -108,7 +110,7 @@ WgradPlan plan_wgrad(int cin, int cout, int ks, const Geo &g) {
 size_t wgrad_scratch_floats(int cin, int cout, int ks, const Geo &g) {
     const WgradPlan w = plan_wgrad(cin, cout, ks, g);
     const size_t a = w.ok ? (size_t)w.S * w.part_stride : 0, b = wgrad_bf16_scratch_floats(cin, cout, ks, g);
-    return a > b ? a : b;
+    return std::max({a, b, wgrad_gemm_f32_scratch_floats(cin, cout, ks, g)});
 }
 
 void conv_wgrad(Ctx &cx, View x, const float *scale_shift, rvn_dtype dt, View dh, int cin, int cout,
@@ -121,6 +123,9 @@ void conv_wgrad(Ctx &cx, View x, const float *scale_shift, rvn_dtype dt, View dh
     if (dt == RVN_BF16 &&
         conv_wgrad_bf16(cx, x, scale_shift, dh, cin, cout, ks, g, scratch, dw, accumulate,
                         P * cin * 4.0 + P * cout * 4.0, flops, defer))
+        return;
+    if (dt == RVN_F32 && conv_wgrad_gemm_f32(cx, x, scale_shift, dh, cin, cout, ks, g, scratch, dw, accumulate,
+                                             P * cin * 4.0 + P * cout * 4.0, flops, defer))
         return;
     WgradLaunch L;
     WgradReduce red{};

@@ -315,6 +315,12 @@ bool conv_dgrad_wgrad_takes_bf16_dh(View x, const uint16_t *dh16, const uint16_t
 bool conv_wgrad_bf16(Ctx &cx, View x, const float *scale_shift, View dh, int cin, int cout, int ks, Geo g,
                      float *scratch, float *dw, bool accumulate, double bytes, double flops, WgradReduce *defer);
 
+// The filter gradient with fp32 operands as a tiled matrix product over the flat pixel index
+// (conv_wgrad_gemm_f32.hip); the contract of conv_wgrad_bf16, scratch of wgrad_gemm_f32_scratch_floats(...) floats.
+size_t wgrad_gemm_f32_scratch_floats(int cin, int cout, int ks, const Geo &g);
+bool conv_wgrad_gemm_f32(Ctx &cx, View x, const float *scale_shift, View dh, int cin, int cout, int ks, Geo g,
+                         float *scratch, float *dw, bool accumulate, double bytes, double flops, WgradReduce *defer);
+
 // ---- fixed-point residual stream (Section 3.2, "Numerical error") ------------
 // A stream element is an int32 code q standing for q * 2^-frac_bits; the Views
 // of stream tensors carry int32 data behind their float pointer.

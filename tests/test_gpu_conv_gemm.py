@@ -18,6 +18,7 @@ CASES = [
     dict(kind="basic", n=1, c=66, h=5, w=13),       # 33 channels, 65 pixels
     dict(kind="basic", n=1, c=66, h=7, w=9),        # 63 pixels
     dict(kind="basic", n=1, c=70, h=2, w=63),       # widest rows of the 128-pixel tile; 35 channels
+    dict(kind="basic", n=2, c=80, h=3, w=95),       # widest rows of the 64-pixel tiles and of the staged runs of `a`
     dict(kind="basic", n=1, c=80, h=2, w=111),      # widest rows of the 32-pixel tile; no backward plan: forward only
     dict(kind="basic", n=1, c=68, h=3, w=1),        # one column: every side tap leaves the image
     dict(kind="bottleneck", n=5, c=136, h=7, w=7, width=33),      # one channel past a 32-channel chunk
