@@ -132,26 +132,34 @@ __global__ __launch_bounds__(kThreads) void conv_bf16_k(const Bf16Args p) {
             const int lr = t % p.lrows, img = t / p.lrows;
             const int n = n0 + img, row = row0 - PAD + lr, col = qx * 4, chb = c0 + oc * 8;
             const bool live = n < N && row >= 0 && row < H;
-            float v[8][4];
+            // Every load is issued, from a clamped address where the item leaves the tensor, and selected
+            // afterwards: a load behind a lane's own condition is waited for before the next is issued.
+            float v[8][4], sc[8], sh[8];
+            const float *const src0 = p.in + (live ? (int64_t)n * p.isn + row * W + col : 0);
+            const int d1 = live ? min(col + 1, W - 1) - col : 0, d2 = live ? min(col + 2, W - 1) - col : 0;
+            const int d3 = live ? min(col + 3, W - 1) - col : 0;
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                v[k][0] = v[k][1] = v[k][2] = v[k][3] = 0.f;
-                if (live && chb + k < CI) {
-                    const float *src = p.in + (int64_t)n * p.isn + (int64_t)(chb + k) * p.isc + row * W + col;
-                    if (vec) {
-                        const float4 q = *reinterpret_cast<const float4 *>(src);
-                        v[k][0] = q.x; v[k][1] = q.y; v[k][2] = q.z; v[k][3] = q.w;
-                    } else {
-                        v[k][0] = src[0];
-                        if (col + 1 < W) v[k][1] = src[1];
-                        if (col + 2 < W) v[k][2] = src[2];
-                        if (col + 3 < W) v[k][3] = src[3];
-                    }
-                    if (p.scale_shift) {
-                        const float sc = p.scale_shift[chb + k], sh = p.scale_shift[CI + chb + k];
+                const int ch = min(chb + k, CI - 1);
+                const float *src = src0 + (int64_t)ch * p.isc;
+                if (vec) {
+                    const float4 q = *reinterpret_cast<const float4 *>(src);
+                    v[k][0] = q.x; v[k][1] = q.y; v[k][2] = q.z; v[k][3] = q.w;
+                } else {
+                    v[k][0] = src[0]; v[k][1] = src[d1]; v[k][2] = src[d2]; v[k][3] = src[d3];
+                }
+                if (p.scale_shift) {
+                    sc[k] = p.scale_shift[ch];
+                    sh[k] = p.scale_shift[CI + ch];
+                }
+            }
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) v[k][j] = fmaxf(fmaf(v[k][j], sc, sh), 0.f);
-                    }
+            for (int k = 0; k < 8; ++k) {
+                const bool in = live && chb + k < CI;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (p.scale_shift) v[k][j] = fmaxf(fmaf(v[k][j], sc[k], sh[k]), 0.f);
+                    v[k][j] = in ? v[k][j] : 0.f;
                 }
             }
             uint16_t *dst = in_lds + ((img * p.lrows + lr) * p.lcols + PAD + col) * REC + oc * 8;
@@ -193,13 +201,12 @@ __global__ __launch_bounds__(kThreads) void conv_bf16_k(const Bf16Args p) {
                 const int ko = co0 + kol, chb = c0 + oc * 8;
                 float v[8];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    v[k] = 0.f;
-                    const int ch = chb + k;
-                    if (ko < CO && ch < CI)
-                        v[k] = p.transposed ? p.w[((int64_t)ch * CO + ko) * KS2 + (KS2 - 1 - tap)]
-                                            : p.w[((int64_t)ko * CI + ch) * KS2 + tap];
+                for (int k = 0; k < 8; ++k) {  // (every load issued, as above)
+                    const int ch = min(chb + k, CI - 1), kc = min(ko, CO - 1);
+                    v[k] = p.w[p.transposed ? ((int64_t)ch * CO + kc) * KS2 + (KS2 - 1 - tap) : ((int64_t)kc * CI + ch) * KS2 + tap];
                 }
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = ko < CO && chb + k < CI ? v[k] : 0.f;
                 uint4 rec;
                 rec.x = pack2(v[0], v[1]);
                 rec.y = pack2(v[2], v[3]);
@@ -242,16 +249,22 @@ __global__ __launch_bounds__(kThreads) void conv_bf16_k(const Bf16Args p) {
         const float *const rsrc = p.ep != EP_STORE ? p.r + (int64_t)o_img[t] * p.rsn + o_pix[t] : nullptr;
 #pragma unroll
         for (int m = 0; m < MT; ++m) {
+            float rv[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) rv[i] = 0.f;
+            if (p.ep != EP_STORE) {  // all skip values requested before the first store (r may alias out)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int ko = min(co0 + m * 32 + 8 * (i >> 2) + 4 * kg + (i & 3), CO - 1);
+                    rv[i] = rsrc[(int64_t)ko * p.rsc];
+                }
+            }
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const int ko = co0 + m * 32 + 8 * (i >> 2) + 4 * kg + (i & 3);
                 if (ko >= CO) continue;
-                float v = acc[m][t][i];
-                if (p.ep != EP_STORE) {
-                    const float rv = rsrc[(int64_t)ko * p.rsc];
-                    v = p.ep == EP_ADD ? rv + v : rv - v;
-                }
-                dst[(int64_t)ko * p.osc] = v;
+                const float v = acc[m][t][i];
+                dst[(int64_t)ko * p.osc] = p.ep == EP_STORE ? v : p.ep == EP_ADD ? rv[i] + v : rv[i] - v;
             }
         }
     }
