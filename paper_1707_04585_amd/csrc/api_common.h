@@ -49,6 +49,7 @@ View view_of(const rvn_tensor *t);
 struct Layer {
     int cin, cout, ks;
 };
+constexpr size_t kSmallPrepBytes = 128 << 10;  // bound on Plan::small_prep of a forward plan (largest: 90112)
 // Workspace layout.  Offsets in bytes from the workspace base.
 struct Plan {
     int L;
@@ -67,6 +68,7 @@ struct Plan {
     // the data gradient; `prep[l]` says whether layer l uses them
     size_t wq_f[3], wq_b[3];
     bool prep[3];
+    size_t small_prep;  // bytes of the forward copies that are there only for the speed of small layers
     // fixed-point residual stream only: the function's input as fp32 and the
     // function's value before it is rounded into the stream
     size_t xf, fout;

@@ -22,7 +22,7 @@ struct C1Args {
     int HW, CI, CO;
     int ep;
     int gpi, groups;  // 4-pixel groups per image and in total
-    int ksteps;       // CI / 16
+    int ksteps;       // ceil(CI / 16)
     int mtiles;       // ceil(CO / 32)
     float *emit;      // per (channel, 128-pixel tile) mean and M2 of the output (EMIT variants; needs whole tiles)
     int ptiles;       // pixel tiles in all
@@ -76,7 +76,9 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
 // starts at H*W - 4 and leaves the pixels it shares with its neighbour to it).
 // IN16 (aligned variant only): `in` holds bf16 already (dense planes, same element strides; no BN
 // prologue): the values a conversion on load would produce, so results are the same bits at half the bytes.
-template <int MTW, int DEPTH, bool GEN, bool EMIT = false, bool IN16 = false>
+// RAGGED (not with IN16): CI is not a multiple of 16.  In the last step the channels past the last one are
+// read from the last one and zeroed (the filter is zero there too, but zero times infinity is not).
+template <int MTW, int DEPTH, bool GEN, bool EMIT = false, bool IN16 = false, bool RAGGED = false>
 __device__ __forceinline__ void conv1x1_bf16_body(const C1Args &p, int bx, int gx, float *red) {
     using F4 = typename std::conditional<GEN, f4u_t, f4a_t>::type;
     const int lane = threadIdx.x & 63;
@@ -108,7 +110,7 @@ __device__ __forceinline__ void conv1x1_bf16_body(const C1Args &p, int bx, int g
     // Addresses are a wavefront-uniform 64-bit part (channel, step) plus a 32-bit
     // per-lane byte offset (image, pixel, channel octet half): the host keeps
     // every tensor slice handed to one launch below 4 GB.
-    static_assert(!(IN16 && GEN), "bf16 input: aligned planes only");
+    static_assert(!(IN16 && (GEN || RAGGED)), "bf16 input: aligned planes only");
     constexpr int kInBytes = IN16 ? 2 : 4;
     const uint32_t in_off = (uint32_t)(((int64_t)n * p.isn + pix + (int64_t)(kg * 8) * p.isc) * kInBytes);
     const char *const in_base = reinterpret_cast<const char *>(p.in);
@@ -169,10 +171,18 @@ __device__ __forceinline__ void conv1x1_bf16_body(const C1Args &p, int bx, int g
         Quad v[8];
         uint4_t a[MTW];
     };
+    const uint32_t pix_off = RAGGED ? (uint32_t)(((int64_t)n * p.isn + pix) * kInBytes) : 0u;
     auto load = [&](Buf &b, int ks) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-            b.v[k] = *reinterpret_cast<const Quad *>(in_base + (int64_t)(ks * 16 + k) * isc_b + in_off);
+        for (int k = 0; k < 8; ++k) {
+            if constexpr (RAGGED) {  // both halves' channels are wavefront-uniform
+                const int lo = min(ks * 16 + k, CI - 1), hi = min(ks * 16 + k + 8, CI - 1);
+                const uint32_t up = (uint32_t)((int64_t)(hi - lo) * isc_b);
+                b.v[k] = *reinterpret_cast<const Quad *>(in_base + (int64_t)lo * isc_b + (pix_off + (kg ? up : 0u)));
+            } else {
+                b.v[k] = *reinterpret_cast<const Quad *>(in_base + (int64_t)(ks * 16 + k) * isc_b + in_off);
+            }
+        }
 #pragma unroll
         for (int m = 0; m < MTW; ++m) {
             const bool has = mt0 + m < p.mtiles;
@@ -203,9 +213,10 @@ __device__ __forceinline__ void conv1x1_bf16_body(const C1Args &p, int bx, int g
         for (int k = 0; k < 8; ++k) {
             float x0 = b.v[k][0], x1 = b.v[k][1], x2 = b.v[k][2], x3 = b.v[k][3];
             if (bn) {
-                const int c = ks * 16 + k;  // wavefront-uniform: scalar loads
-                const float s_lo = p.scale_shift[c], s_hi = p.scale_shift[c + 8];
-                const float h_lo = p.scale_shift[CI + c], h_hi = p.scale_shift[CI + c + 8];
+                const int c = RAGGED ? min(ks * 16 + k, CI - 1) : ks * 16 + k;  // wavefront-uniform: scalar loads
+                const int c8 = RAGGED ? min(ks * 16 + k + 8, CI - 1) : c + 8;
+                const float s_lo = p.scale_shift[c], s_hi = p.scale_shift[c8];
+                const float h_lo = p.scale_shift[CI + c], h_hi = p.scale_shift[CI + c8];
                 const float sc = kg ? s_hi : s_lo, sh = kg ? h_hi : h_lo;
                 x0 = fmaxf(fmaf(x0, sc, sh), 0.f);
                 x1 = fmaxf(fmaf(x1, sc, sh), 0.f);
@@ -213,6 +224,14 @@ __device__ __forceinline__ void conv1x1_bf16_body(const C1Args &p, int bx, int g
                 x3 = fmaxf(fmaf(x3, sc, sh), 0.f);
             }
             v[k][0] = x0; v[k][1] = x1; v[k][2] = x2; v[k][3] = x3;
+        }
+        if (RAGGED && ks * 16 + 16 > CI) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const bool in = ks * 16 + kg * 8 + k < CI;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[k][j] = in ? v[k][j] : 0.f;
+            }
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {

@@ -68,9 +68,18 @@ int check_geo(int64_t n, int64_t h, int64_t w) {
 // every workgroup of the convolution.
 bool wants_prep(const rvn_block_desc &d, const Layer &ly, const Geo &g) {
     if (d.conv_dtype != RVN_BF16) return false;
-    if (ly.ks == 1 && (conv1x1_direct_ok(ly.cin, g) || conv1x1_direct_ok(ly.cout, g))) return true;
+    auto whole_steps = [&](int k) { return k % 16 == 0 && conv1x1_direct_ok(k, g); };
+    if (ly.ks == 1 && (whole_steps(ly.cin) || whole_steps(ly.cout))) return true;
     if (ly.ks == 3 && (conv3x3_bf16_ok(ly.cin, ly.cout, g) || conv3x3_bf16_ok(ly.cout, ly.cin, g))) return true;
     return (int64_t)ly.cin * ly.cout * ly.ks * ly.ks >= 16384;
+}
+
+// Smaller 1x1 filters of other channel counts: for the 1x1 kernel's sake, up to the usual reduction to a
+// quarter (beyond it the padded copy grows past what the filter is worth).  At most kSmallPrepBytes of
+// forward copies per function: two filters of fewer than 16384 elements, sides of ratio 4 padded to 32 and 16.
+bool wants_small_prep(const rvn_block_desc &d, const Layer &ly, const Geo &g) {
+    return d.conv_dtype == RVN_BF16 && ly.ks == 1 && std::max(ly.cin, ly.cout) <= 4 * std::min(ly.cin, ly.cout) &&
+           (conv1x1_direct_ok(ly.cin, g) || conv1x1_direct_ok(ly.cout, g));
 }
 
 Plan make_plan(const rvn_block_desc &d, const Geo &g, bool backward, bool fixed) {
@@ -93,10 +102,12 @@ Plan make_plan(const rvn_block_desc &d, const Geo &g, bool backward, bool fixed)
     }
     for (int l = 0; l < p.L; ++l) {
         const Layer &ly = p.layers[l];
-        p.prep[l] = wants_prep(d, ly, g);
+        const bool large = wants_prep(d, ly, g);
+        p.prep[l] = large || wants_small_prep(d, ly, g);
         if (!p.prep[l]) continue;
         p.wq_f[l] = off;
         off = align_up(off + filter_bf16_elems(ly.cout, ly.cin, ly.ks) * 2);
+        if (!large) p.small_prep += off - p.wq_f[l];
         if (backward) {
             p.wq_b[l] = off;
             off = align_up(off + filter_bf16_elems(ly.cin, ly.cout, ly.ks) * 2);

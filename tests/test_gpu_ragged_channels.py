@@ -1,0 +1,61 @@
+"""bf16 bottleneck blocks whose channel counts are not whole 16-channel steps of the 1x1 kernel: the last
+step's missing channels must contribute nothing, forward and as a data gradient, whatever lies next to the
+tensor.  Held to the bf16 bars of the parity cases (forward and reconstruction 1e-2, gradients 2e-2, or 1.5 x the
+difference of two oracle evaluations where that is larger); the channels next to the stream are infinite."""
+import numpy as np
+import pytest
+
+import synth_inputs as S
+from bf16_floor import bf16_grad_floor
+from oracle import revnet_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    dict(n=3, c=34, h=9, w=9, width=17),       # one channel past a step on both sides, planes of 81 pixels
+    dict(n=2, c=62, h=16, w=16, width=16),     # a step short of one channel; the other side whole
+    dict(n=8, c=200, h=14, w=14, width=44),    # channels shared over the wavefronts of a workgroup
+    dict(n=40, c=130, h=28, w=28, width=36),   # two output tiles per wavefront, statistics from the epilogue
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda k: "n%d c%d/%d %dx%d" % (k["n"], k["c"], k["width"], k["h"], k["w"]))
+def test_bottleneck_block(case):
+    import torch
+    import paper_1707_04585_amd as rv
+    from paper_1707_04585_amd.torch_harness import StackRunner, download_grads
+    cfg = dict(kind="bottleneck", depth=1, conv="bf16", affine="random")
+    cfg.update(case)
+    x, params, dy = S.draw_stack(S.BASE_SEED + 1616, **cfg)
+    n, c, h, w = cfg["n"], cfg["c"], cfg["h"], cfg["w"]
+    print(case, flush=True)
+    r = StackRunner(**cfg)
+    r.set_params(params)
+
+    def halves(src):  # each half followed by 16 channels of infinities, per image
+        out = []
+        for part in (src[:, :c // 2], src[:, c // 2:]):
+            t = torch.full((n, c // 2 + 16, h, w), float("inf"), dtype=torch.float32, device=r.device)
+            t[:, :c // 2] = torch.as_tensor(np.ascontiguousarray(part, dtype=np.float32)).to(r.device)
+            out.append(t[:, :c // 2])
+        return out
+
+    host = lambda p: np.concatenate([t.cpu().numpy() for t in p], 1)
+    X, D = halves(x), halves(dy)
+    rv.revnet_stack_fwd(r.desc, 1, *X, r.params, *X, r.ws)
+    torch.cuda.synchronize()
+    y = host(X)
+    rv.revnet_stack_bwd(r.desc, 1, *X, *D, r.params, *X, *D, r.grads, 0, r.ws)
+    torch.cuda.synchronize()
+    sp = lambda t: (np.ascontiguousarray(t[:, :c // 2]), np.ascontiguousarray(t[:, c // 2:]))
+    with O.conv_operands("bf16"):
+        y1, y2, _, stored = O.stack_fwd(*sp(x), params, keep=True)
+        dx1, dx2, ref = O.stack_bwd_stored(stored, params, *sp(dy))
+    assert O.rel_l2(y, np.concatenate([y1, y2], 1)) < 1e-2
+    assert O.rel_l2(host(X), x) < 1e-2
+    floor = bf16_grad_floor(O, cfg, x, params, dy, dict(dx=np.concatenate([dx1, dx2], 1)))
+    bar = max(2e-2, 1.5 * floor)
+    errs = dict(dx=O.rel_l2(host(D), np.concatenate([dx1, dx2], 1)),
+                w=O.rel_l2(O.flatten_grads(download_grads(r.grads)), O.flatten_grads(ref)))
+    print(errs, "bar", bar, flush=True)
+    assert max(errs.values()) < bar, errs
