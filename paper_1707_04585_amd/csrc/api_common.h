@@ -49,7 +49,7 @@ View view_of(const rvn_tensor *t);
 struct Layer {
     int cin, cout, ks;
 };
-constexpr size_t kSmallPrepBytes = 128 << 10;  // bound on Plan::small_prep of a forward plan (largest: 90112)
+constexpr size_t kSmallPrepBytes = 128 << 10;  // bound on Plan::small_prep of a forward plan
 // Workspace layout.  Offsets in bytes from the workspace base.
 struct Plan {
     int L;

@@ -37,10 +37,10 @@ namespace {
 
 using namespace c3;
 
-template <int WM, int MTW, int NTW, int KC, bool EMIT = false, int NI = kInItems>
+template <int WM, int MTW, int NTW, int KC, bool EMIT, int NI, bool RAGGED>
 __global__ __launch_bounds__(kThreads, 2) void conv3x3_bf16_k(const C3Args p) {
     extern __shared__ __align__(16) uint16_t smem16[];
-    conv3x3_bf16_body<WM, MTW, NTW, KC, EMIT, NI>(p, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z, smem16);
+    conv3x3_bf16_body<WM, MTW, NTW, KC, EMIT, NI, false, RAGGED>(p, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z, smem16);
 }
 
 // out = ep(r, sum_s part[s]) over dense partial tiles [S][n][c][hw], summed in
@@ -93,7 +93,9 @@ struct C3Plan {
 C3Plan plan_c3(int ci, int co, const Geo &g, int stride = 1) {
     C3Plan pl{};
     pl.ok = false;
-    if (ci % 8 != 0 || g.w < 4 || ci > 4096) return pl;
+    if (g.w < 4 || ci > 4096) return pl;
+    const bool ragged = ci % 8 != 0;  // (the stride-2 form and the shared launches take whole octets only)
+    if (ragged && stride != 1) return pl;
     if (stride != 1 && (stride != 2 || g.h % 2 || g.w % 2)) return pl;
     const int oh = g.h / stride, ow = g.w / stride;  // the result's rows and columns
     // Output channels per workgroup and the wavefront arrangement.
@@ -132,6 +134,13 @@ C3Plan plan_c3(int ci, int co, const Geo &g, int stride = 1) {
     pl.chunks = (ci + pl.KC - 1) / pl.KC;
     const int64_t wgs = (int64_t)((g.n + pl.IMGS - 1) / pl.IMGS) * pl.bands * ((co + ch - 1) / ch);
     pl.S = 1;
+    // Ragged octets: taken where the unsplit launch fills the chip (66 -> 66 channels in two bottleneck
+    // blocks, 64 images of 56x56: 4.76 ms per training step with conv_bf16_k, 4.34 with this kernel); below
+    // that, conv_bf16_k has smaller pixel blocks and needs no partial tiles.
+    if (ragged && wgs <= 128) {
+        pl.ok = false;
+        return pl;
+    }
     // Too few workgroups for the chip (measured: at most one per two compute
     // units): split the input channels over gridDim.z as well.  (56 -> 56 channels at 8x8, N=128: the
     // 32 unsplit workgroups take 18.5 us, the 64 split ones 10.1 us plus 4.2 us for the sum.)
@@ -155,17 +164,24 @@ bool raise_lds_limit(Ctx &cx, K kernel, bool &raised) {
     return true;
 }
 
-template <int WM, int MTW, int NTW, int KC, bool EMIT, int NI>
+template <int WM, int MTW, int NTW, int KC, bool EMIT, int NI, bool RAGGED>
 void launch_c3_items(Ctx &cx, const C3Launch &L, dim3 grid) {
     static bool raised = false;
-    if (!raise_lds_limit(cx, conv3x3_bf16_k<WM, MTW, NTW, KC, EMIT, NI>, raised)) return;
-    cx.run(conv3x3_bf16_k<WM, MTW, NTW, KC, EMIT, NI>, grid, dim3(kThreads), L.lds_bytes, L.a);
+    if (!raise_lds_limit(cx, conv3x3_bf16_k<WM, MTW, NTW, KC, EMIT, NI, RAGGED>, raised)) return;
+    cx.run(conv3x3_bf16_k<WM, MTW, NTW, KC, EMIT, NI, RAGGED>, grid, dim3(kThreads), L.lds_bytes, L.a);
 }
 
 template <int WM, int MTW, int NTW, int KC, bool EMIT>
 void launch_c3_variant(Ctx &cx, const C3Launch &L, dim3 grid) {
-    if (L.NI == 1) launch_c3_items<WM, MTW, NTW, KC, EMIT, 1>(cx, L, grid);
-    else launch_c3_items<WM, MTW, NTW, KC, EMIT, kInItems>(cx, L, grid);
+    if constexpr (KC == 16) {
+        if (L.a.CI % 8 != 0) {
+            if (L.NI == 1) launch_c3_items<WM, MTW, NTW, KC, EMIT, 1, true>(cx, L, grid);
+            else launch_c3_items<WM, MTW, NTW, KC, EMIT, kInItems, true>(cx, L, grid);
+            return;
+        }
+    }
+    if (L.NI == 1) launch_c3_items<WM, MTW, NTW, KC, EMIT, 1, false>(cx, L, grid);
+    else launch_c3_items<WM, MTW, NTW, KC, EMIT, kInItems, false>(cx, L, grid);
 }
 
 template <int WM, int MTW, int NTW, int KC>

@@ -94,10 +94,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_over(const void *base, 
 // memory round trip, so with one chunk of lookahead every chunk paid for one.
 // IN16: `in` holds bf16 already (dense planes, same element strides; no BN prologue): the values a
 // conversion on load would produce, so results are the same bits at half the bytes.
-template <int WM, int MTW, int NTW, int KC, bool EMIT = false, int NI = kInItems, bool IN16 = false>
+// RAGGED (KC = 16, not with IN16): CI is not a multiple of 8.  The channels that the last octet lacks are read
+// from the last channel and zeroed, as the padded filter is (zero times infinity is not zero).
+template <int WM, int MTW, int NTW, int KC, bool EMIT = false, int NI = kInItems, bool IN16 = false, bool RAGGED = false>
 __device__ __forceinline__ void conv3x3_bf16_body(const C3Args &p, int bx_launch, int by, int bz, int gz, uint16_t *smem16) {
     constexpr int WN = 4 / WM;
     constexpr int REC = KC + kPadK, OCTS = KC / 8;
+    static_assert(!RAGGED || (KC == 16 && !IN16), "ragged channels");
     constexpr int CH = WM * MTW * 32;  // output channels per workgroup
     constexpr int W_ITEMS = CH * 9 * OCTS, W_PER = (W_ITEMS + kThreads - 1) / kThreads;
     uint16_t *in_lds = smem16;                                    // [IMGS][lrows][lcols][REC]
@@ -193,8 +196,15 @@ __device__ __forceinline__ void conv3x3_bf16_body(const C3Args &p, int bx_launch
             // octets past the last channel read the chunk's first octet instead and are zeroed later
             const uint32_t off = it_off[i] + (c0 + oc * 8 < CI ? (uint32_t)(oc * 8 * isc_b) : 0u);
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
-                g[i][k] = *reinterpret_cast<const Quad *>(in_base + (int64_t)(c0 + k) * isc_b + off);
+            for (int k = 0; k < 8; ++k) {
+                if constexpr (RAGGED) {  // both octets' channels are wavefront-uniform
+                    const int lo = min(c0 + k, CI - 1), hi = min(c0 + 8 + k, CI - 1);
+                    const uint32_t up = (uint32_t)((int64_t)(hi - lo) * isc_b);
+                    g[i][k] = *reinterpret_cast<const Quad *>(in_base + (int64_t)lo * isc_b + (it_off[i] + (oc ? up : 0u)));
+                } else {
+                    g[i][k] = *reinterpret_cast<const Quad *>(in_base + (int64_t)(c0 + k) * isc_b + off);
+                }
+            }
         }
     };
     auto g2r_w = [&](int c0) {
@@ -214,7 +224,7 @@ __device__ __forceinline__ void conv3x3_bf16_body(const C3Args &p, int bx_launch
             const int info = it_info[i];
             const int col = info & 0xffff, nvalid = (info >> 16) & 15, oc = info >> 24;
             if (nvalid == 0) continue;
-            const bool chan_ok = c0 + oc * 8 < CI;
+            const bool octet_ok = c0 + oc * 8 < CI;
             if constexpr (IN16) {
                 // dword w of channel k holds pixels 2w, 2w + 1; a record wants, per pixel, the channels in
                 // pairs: one byte permute per dword (low halves for even pixels, high halves for odd ones)
@@ -226,7 +236,7 @@ __device__ __forceinline__ void conv3x3_bf16_body(const C3Args &p, int bx_launch
 #pragma unroll
                     for (int d = 0; d < 4; ++d) {
                         const uint32_t pr = __builtin_amdgcn_perm(g[i][2 * d + 1][j >> 1], g[i][2 * d][j >> 1], sel);
-                        q[d] = chan_ok ? pr : 0u;
+                        q[d] = octet_ok ? pr : 0u;
                     }
                     *reinterpret_cast<uint4_t *>(in_lds + rec * REC + oc * 8) = q;
                 }
@@ -237,6 +247,7 @@ __device__ __forceinline__ void conv3x3_bf16_body(const C3Args &p, int bx_launch
             for (int k = 0; k < 8; ++k) {
                 const f4u_t x = g[i][k];
                 float x0 = x[0], x1 = x[1], x2 = x[2], x3 = x[3];
+                const bool chan_ok = RAGGED ? c0 + oc * 8 + k < CI : octet_ok;
                 if (bn) {
                     const int ch = chan_ok ? c0 + oc * 8 + k : 0;
                     const float sc = ss_lds[ch], sh = ss_lds[CI + ch];

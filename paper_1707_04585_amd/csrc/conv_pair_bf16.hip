@@ -137,7 +137,7 @@ bool pair_small(Ctx &cx, View x, const float *scale_shift, View dh, const uint16
     WgradLaunch W;
     WgradReduce red{};
     if (!conv_wgrad_plan(x, scale_shift, true, dh, cin, cout, 3, g, wgrad_scratch, dw, accumulate, W, red)) return false;
-    if (W.mt != 1 || W.ct != 1 || !W.vec) return false;
+    if (W.mt != 1 || W.ct != 1 || !W.vec || cout % 8 != 0) return false;
     C3Launch C;
     if (!conv3x3_bf16_plan(dh, nullptr, wq_b, cout, cin, g, EP_STORE, nullptr, dense_view(da, cin, g), conv_scratch, C))
         return false;
@@ -186,6 +186,7 @@ bool plan_pair(View x, const float *scale_shift, View dh, const uint16_t *wq_b, 
     P.q = PairGrid{};
     P.lds = P.W.lds_bytes;
     if (ks == 3) {
+        if (cout % 8 != 0) return false;  // no instance for a last octet of fewer channels
         if (!conv3x3_bf16_plan(dh, nullptr, wq_b, cout, cin, g, EP_STORE, nullptr, out, conv_scratch, P.C3)) return false;
         // rows that are not whole 4-pixel groups: instantiated for the wide layers only (64 channels per workgroup, chunks of 16)
         if (!P.W.vec && (P.C3.MTW != 2 || P.C3.KC != 16)) return false;

@@ -70,15 +70,19 @@ bool wants_prep(const rvn_block_desc &d, const Layer &ly, const Geo &g) {
     if (d.conv_dtype != RVN_BF16) return false;
     auto whole_steps = [&](int k) { return k % 16 == 0 && conv1x1_direct_ok(k, g); };
     if (ly.ks == 1 && (whole_steps(ly.cin) || whole_steps(ly.cout))) return true;
-    if (ly.ks == 3 && (conv3x3_bf16_ok(ly.cin, ly.cout, g) || conv3x3_bf16_ok(ly.cout, ly.cin, g))) return true;
+    auto whole_octets = [&](int ci, int co) { return ci % 8 == 0 && conv3x3_bf16_ok(ci, co, g); };
+    if (ly.ks == 3 && (whole_octets(ly.cin, ly.cout) || whole_octets(ly.cout, ly.cin))) return true;
     return (int64_t)ly.cin * ly.cout * ly.ks * ly.ks >= 16384;
 }
 
-// Smaller 1x1 filters of other channel counts: for the 1x1 kernel's sake, up to the usual reduction to a
-// quarter (beyond it the padded copy grows past what the filter is worth).  At most kSmallPrepBytes of
-// forward copies per function: two filters of fewer than 16384 elements, sides of ratio 4 padded to 32 and 16.
+// Smaller filters of other channel counts, for the sake of the kernels that read prepared filters; 1x1 up to
+// the usual reduction to a quarter (beyond it the padded copy grows past what the filter is worth).  At
+// most kSmallPrepBytes of forward copies per function: filters of fewer than 16384 elements, padded to 32 rows
+// and 16 columns (1x1, two of them: 90112) or to 8 columns (3x3: 36288 each).
 bool wants_small_prep(const rvn_block_desc &d, const Layer &ly, const Geo &g) {
-    return d.conv_dtype == RVN_BF16 && ly.ks == 1 && std::max(ly.cin, ly.cout) <= 4 * std::min(ly.cin, ly.cout) &&
+    if (d.conv_dtype != RVN_BF16) return false;
+    if (ly.ks == 3) return conv3x3_bf16_ok(ly.cin, ly.cout, g) || conv3x3_bf16_ok(ly.cout, ly.cin, g);
+    return std::max(ly.cin, ly.cout) <= 4 * std::min(ly.cin, ly.cout) &&
            (conv1x1_direct_ok(ly.cin, g) || conv1x1_direct_ok(ly.cout, g));
 }
 

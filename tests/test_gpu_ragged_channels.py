@@ -1,5 +1,5 @@
-"""bf16 bottleneck blocks whose channel counts are not whole 16-channel steps of the 1x1 kernel: the last
-step's missing channels must contribute nothing, forward and as a data gradient, whatever lies next to the
+"""bf16 blocks whose channel counts are not whole 16-channel steps of the 1x1 kernel or whole 8-channel octets
+of the 3x3 kernel: the last step's missing channels must contribute nothing, forward and as a data gradient, whatever lies next to the
 tensor.  Held to the bf16 bars of the parity cases (forward and reconstruction 1e-2, gradients 2e-2, or 1.5 x the
 difference of two oracle evaluations where that is larger); the channels next to the stream are infinite."""
 import numpy as np
@@ -15,16 +15,19 @@ CASES = [
     dict(n=3, c=34, h=9, w=9, width=17),       # one channel past a step on both sides, planes of 81 pixels
     dict(n=2, c=62, h=16, w=16, width=16),     # a step short of one channel; the other side whole
     dict(n=8, c=200, h=14, w=14, width=44),    # channels shared over the wavefronts of a workgroup
+    dict(n=48, c=136, h=28, w=28, width=35),   # 3x3 on its own kernel: two octets and three channels past
+    dict(kind="basic", n=132, c=26, h=16, w=16),   # 13 channels
+    dict(kind="basic", n=70, c=90, h=15, w=14),    # 45 channels, rows of two pixels past whole 4-pixel groups
     dict(n=40, c=130, h=28, w=28, width=36),   # two output tiles per wavefront, statistics from the epilogue
 ]
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda k: "n%d c%d/%d %dx%d" % (k["n"], k["c"], k["width"], k["h"], k["w"]))
-def test_bottleneck_block(case):
+@pytest.mark.parametrize("case", CASES, ids=lambda k: "n%d c%d/%d %dx%d" % (k["n"], k["c"], k.get("width", 0), k["h"], k["w"]))
+def test_block(case):
     import torch
     import paper_1707_04585_amd as rv
     from paper_1707_04585_amd.torch_harness import StackRunner, download_grads
-    cfg = dict(kind="bottleneck", depth=1, conv="bf16", affine="random")
+    cfg = dict(kind="bottleneck", width=None, depth=1, conv="bf16", affine="random")
     cfg.update(case)
     x, params, dy = S.draw_stack(S.BASE_SEED + 1616, **cfg)
     n, c, h, w = cfg["n"], cfg["c"], cfg["h"], cfg["w"]
