@@ -122,12 +122,12 @@ void launch_conv(Ctx &cx, ConvArgs &a, const Tiling &tl, int mt, dim3 grid) {
 
 void conv_mfma(Ctx &cx, View in, const float *scale_shift, const float *w, bool transposed, int ci,
                int co, int ks, Geo g, bool bf16, Epilogue ep, const View *r, View out) {
-    if (!bf16 && conv_gemm_f32(cx, in, scale_shift, w, transposed, ci, co, ks, g, ep, r, out)) return;
     ConvLaunch L;
     if (!conv_mfma_plan(in, scale_shift, w, transposed, ci, co, ks, g, bf16, ep, r, out, L)) {
         cx.fail(hipErrorInvalidConfiguration);  // no tiling fits (image rows too wide for LDS)
         return;
     }
+    if (!bf16 && conv_gemm_f32(cx, in, scale_shift, w, transposed, ci, co, ks, g, ep, r, out)) return;
     Tiling tl{};
     tl.NT = L.nt;
     tl.lds_bytes = L.lds_bytes;
