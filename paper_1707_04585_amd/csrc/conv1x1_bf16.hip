@@ -144,6 +144,7 @@ bool conv1x1_bf16(Ctx &cx, View in, const float *scale_shift, const uint16_t *wq
     if (!wq || !conv1x1_direct_ok(ci, g)) return false;
     const int slice_n = images_per_launch(in, r, out, ci, co, g);
     if (slice_n == 0) {  // one image alone is too large
+        if (ci % 16 != 0) return false;
         cx.fail(hipErrorInvalidValue);
         return true;
     }

@@ -382,7 +382,10 @@ void prep_filters_bf16(Ctx &cx, const PrepArgs &a, double bytes) {
 
 bool conv_bf16(Ctx &cx, View in, const float *scale_shift, const float *w, const uint16_t *wq, bool transposed,
                int ci, int co, int ks, Geo g, Epilogue ep, const View *r, View out, float *scratch) {
-    if (ks == 1 && wq && conv1x1_direct_ok(ci, g)) return conv1x1_bf16(cx, in, scale_shift, wq, ci, co, g, ep, r, out);
+    if (ks == 1 && wq && conv1x1_direct_ok(ci, g)) {
+        if (conv1x1_bf16(cx, in, scale_shift, wq, ci, co, g, ep, r, out)) return true;
+        wq = nullptr;  // ragged channels with images of 4 GiB or more: 64-bit offsets below, filter in its own layout
+    }
     if (ks == 3 && wq && conv3x3_bf16(cx, in, scale_shift, wq, ci, co, g, ep, r, out, scratch)) return true;
     const Bf16Plan pl = plan_bf16(ci, co, ks, g);
     if (!pl.ok) return false;
