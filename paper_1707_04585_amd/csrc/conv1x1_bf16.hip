@@ -44,8 +44,10 @@ void launch_c1(Ctx &cx, const C1Launch &L) {
     const C1Args &a = L.a;
     const dim3 grid(L.wgs);
     if (a.emit) {  // (never the general variant)
-        if (L.mtw == 2) cx.run(conv1x1_bf16_k<2, 1, false, true, RAGGED>, grid, dim3(kThreads), L.lds_bytes, a);
-        else cx.run(conv1x1_bf16_k<1, 2, false, true, RAGGED>, grid, dim3(kThreads), L.lds_bytes, a);
+        if constexpr (!RAGGED) {
+            if (L.mtw == 2) cx.run(conv1x1_bf16_k<2, 1, false, true, false>, grid, dim3(kThreads), L.lds_bytes, a);
+            else cx.run(conv1x1_bf16_k<1, 2, false, true, false>, grid, dim3(kThreads), L.lds_bytes, a);
+        }
     } else if (L.mtw == 2) {
         if (L.gen) cx.run(conv1x1_bf16_k<2, 1, true, false, RAGGED>, grid, dim3(kThreads), L.lds_bytes, a);
         else cx.run(conv1x1_bf16_k<2, 1, false, false, RAGGED>, grid, dim3(kThreads), L.lds_bytes, a);
@@ -157,7 +159,10 @@ bool conv1x1_bf16(Ctx &cx, View in, const float *scale_shift, const uint16_t *wq
         C1Args &a = L.a;
         // Statistics of the output for the BN layer that reads it next: whole 128-pixel tiles, aligned
         // variant, one launch for all images (with channel shares the wavefront holding the final sums emits).
-        const bool emits = cx.want_emit && cx.emit_buf && !L.gen && a.groups % 32 == 0 && ns == g.n &&
+        // Not for ragged channel counts: their statistics come from a pass over the tensor, which rounds less
+        // (68 and 34 channels, 4 images of 16x16, gradients of a block against 64 bits, mean of 100 draws:
+        // 1.28e-2 with statistics from the tiles' moments, 8.7e-3 from the pass).
+        const bool emits = ci % 16 == 0 && cx.want_emit && cx.emit_buf && !L.gen && a.groups % 32 == 0 && ns == g.n &&
                            (size_t)co * a.ptiles * 2 <= cx.emit_floats;
         a.emit = emits ? cx.emit_buf : nullptr;
         if (emits) cx.emitted = EmittedStats{out.p, out.sn, out.sc, co, g.n, g.h, g.w, a.ptiles, 128};

@@ -76,8 +76,10 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
 // starts at H*W - 4 and leaves the pixels it shares with its neighbour to it).
 // IN16 (aligned variant only): `in` holds bf16 already (dense planes, same element strides; no BN
 // prologue): the values a conversion on load would produce, so results are the same bits at half the bytes.
-// RAGGED (not with IN16): CI is not a multiple of 16.  In the last step the channels past the last one are
-// read from the last one and zeroed (the filter is zero there too, but zero times infinity is not).
+// RAGGED (not with IN16 or EMIT): CI is not a multiple of 16.  In the last step the channels past the last one
+// are read from the last one and zeroed (the filter is zero there too, but zero times infinity is not).  The
+// skip operand is added to the finished sum, as conv_bf16_k does, which this variant stands in for: without
+// channel shares the results are its bits.
 template <int MTW, int DEPTH, bool GEN, bool EMIT = false, bool IN16 = false, bool RAGGED = false>
 __device__ __forceinline__ void conv1x1_bf16_body(const C1Args &p, int bx, int gx, float *red) {
     using F4 = typename std::conditional<GEN, f4u_t, f4a_t>::type;
@@ -111,6 +113,7 @@ __device__ __forceinline__ void conv1x1_bf16_body(const C1Args &p, int bx, int g
     // per-lane byte offset (image, pixel, channel octet half): the host keeps
     // every tensor slice handed to one launch below 4 GB.
     static_assert(!(IN16 && (GEN || RAGGED)), "bf16 input: aligned planes only");
+    static_assert(!(EMIT && RAGGED), "no statistics from the ragged variant");
     constexpr int kInBytes = IN16 ? 2 : 4;
     const uint32_t in_off = (uint32_t)(((int64_t)n * p.isn + pix + (int64_t)(kg * 8) * p.isc) * kInBytes);
     const char *const in_base = reinterpret_cast<const char *>(p.in);
@@ -137,7 +140,7 @@ __device__ __forceinline__ void conv1x1_bf16_body(const C1Args &p, int bx, int g
     // the tensor base, and the value is discarded afterwards): a load inside a divergent branch makes the
     // compiler wait for it before the next one is issued, one memory round trip per register.
     float16_t acc[MTW][4];
-    if (p.ep != EP_STORE) {
+    if (!RAGGED && p.ep != EP_STORE) {
         const bool fetch = live && !idle && kw == 0;
         const float sign = p.ep == EP_SUB ? -1.f : 1.f;
         F4 t[MTW][16];
@@ -317,12 +320,27 @@ __device__ __forceinline__ void conv1x1_bf16_body(const C1Args &p, int bx, int g
 #pragma unroll
     for (int m = 0; m < MTW; ++m) {
         float ea[16], eb[16], piv[16];
+        if (RAGGED && p.ep != EP_STORE) {  // (every load before the first store)
+            F4 rv[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const bool ok = chan(m, i) + 4 * kg < p.CO;
+                rv[i] = *reinterpret_cast<const F4 *>(r_base + (ok ? (int64_t)chan(m, i) * p.rsc * 4 + r_off : 0));
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float a = acc[m][j][i];
+                    acc[m][j][i] = p.ep == EP_ADD ? rv[i][j] + a : rv[i][j] - a;
+                }
+        }
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             ea[i] = eb[i] = piv[i] = 0.f;
             if (chan(m, i) + 4 * kg >= p.CO) continue;
             F4 t = {acc[m][0][i], acc[m][1][i], acc[m][2][i], acc[m][3][i]};
-            if (p.ep == EP_SUB) t = -t;
+            if (!RAGGED && p.ep == EP_SUB) t = -t;
             float *op = reinterpret_cast<float *>(o_base + (int64_t)chan(m, i) * p.osc * 4 + o_off);
             if (!GEN || dup == 0) {
                 *reinterpret_cast<F4 *>(op) = t;

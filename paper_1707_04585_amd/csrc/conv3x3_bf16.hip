@@ -174,9 +174,9 @@ void launch_c3_items(Ctx &cx, const C3Launch &L, dim3 grid) {
 template <int WM, int MTW, int NTW, int KC, bool EMIT>
 void launch_c3_variant(Ctx &cx, const C3Launch &L, dim3 grid) {
     if constexpr (KC == 16) {
-        if (L.a.CI % 8 != 0) {
-            if (L.NI == 1) launch_c3_items<WM, MTW, NTW, KC, EMIT, 1, true>(cx, L, grid);
-            else launch_c3_items<WM, MTW, NTW, KC, EMIT, kInItems, true>(cx, L, grid);
+        if (L.a.CI % 8 != 0) {  // (without EMIT)
+            if (L.NI == 1) launch_c3_items<WM, MTW, NTW, KC, false, 1, true>(cx, L, grid);
+            else launch_c3_items<WM, MTW, NTW, KC, false, kInItems, true>(cx, L, grid);
             return;
         }
     }
@@ -269,7 +269,8 @@ bool conv3x3_bf16(Ctx &cx, View in, const float *scale_shift, const uint16_t *wq
     // conv3x3_bf16_finish), and every pixel slot of every workgroup a valid pixel (whole blocks of rows or images).
     const int slots = 4 * 2 * 32, tiles = a.wg_x * 4;
     const bool whole = a.n_pix == slots && g.n % a.IMGS == 0 && g.h % a.TR == 0;
-    if (cx.want_emit && cx.emit_buf && L.S == 1 && whole && (size_t)co * tiles * 2 <= cx.emit_floats) {
+    // (not for ragged channel counts, as in conv1x1_bf16)
+    if (ci % 8 == 0 && cx.want_emit && cx.emit_buf && L.S == 1 && whole && (size_t)co * tiles * 2 <= cx.emit_floats) {
         a.emit = cx.emit_buf;
         a.emit_tiles = tiles;
         cx.emitted = EmittedStats{out.p, out.sn, out.sc, co, g.n, g.h, g.w, tiles, 64};

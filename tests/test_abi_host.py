@@ -151,6 +151,15 @@ def test_workspace_does_not_depend_on_depth_and_scales_with_batch():
     assert abs(c50[1]["algorithmic_bytes"] - (c1[1]["algorithmic_bytes"] + 49 * per_block_bytes)) < 1e-6 * c50[1]["algorithmic_bytes"]
 
 
+@pytest.mark.parametrize("kind,c,width", [("basic", 66, 0), ("bottleneck", 136, 34)])
+def test_ragged_bf16_layers_take_their_statistics_from_a_pass_over_the_tensor(kind, c, width):
+    """bf16 channel counts off the 8- and 16-channel steps: 32 rows cut into whole tiles and 31 do not, and the bytes
+    per pixel are the same (statistics merged from tile moments would spare a read of the tensor)."""
+    d = rv.BlockDesc(kind, c // 2, width, conv_dtype="bf16")
+    per_pixel = [rv.revnet_stack_cost(d, 2, 40, h, 32)[0]["algorithmic_bytes"] / (40 * h * 32) for h in (32, 31)]
+    assert abs(per_pixel[0] / per_pixel[1] - 1) < 0.01, per_pixel
+
+
 def test_down_block_and_body_argument_validation():
     """The subsampling block and the body check shapes, channel chains, even
     sizes, overlaps and the workspace before anything is enqueued."""

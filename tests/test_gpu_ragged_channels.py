@@ -85,3 +85,27 @@ def test_image_of_four_gib():
         return [t.as_strided((1, c // 2, h, w), (1 << 30, h * w, w, 1)) for t in flat]
 
     check_block(cfg, x, params, dy, halves)
+
+
+@pytest.mark.parametrize("shape", [(200, 44, 9, 9), (136, 34, 16, 16), (72, 18, 14, 14), (34, 17, 7, 7), (220, 100, 6, 11)],
+                         ids=lambda k: "c%d/%d %dx%d" % k)
+def test_forward_bits_are_those_of_the_general_kernel(shape):
+    """Up to 112 channels (no channel shares) the register-operand 1x1 kernel adds in the general kernel's order, skip
+    operand last, and both leave the statistics to a pass over the tensor: an image with a batch stride
+    of 4 GiB, which takes the general kernel, gives the same bits as a dense one."""
+    import torch
+    import paper_1707_04585_amd as rv
+    from paper_1707_04585_amd.torch_harness import StackRunner
+    c, width, h, w = shape
+    cfg = dict(kind="bottleneck", n=1, c=c, h=h, w=w, width=width, depth=2, conv="bf16", affine="random")
+    x, params, _ = S.draw_stack(S.BASE_SEED + 1618, **cfg)
+    r = StackRunner(**cfg)
+    r.set_params(params)
+    got = []
+    for sn in (c // 2 * h * w, 1 << 30):
+        X = [torch.as_tensor(np.ascontiguousarray(p, dtype=np.float32)).to(r.device).as_strided((1, c // 2, h, w), (sn, h * w, w, 1))
+             for p in (x[:, :c // 2], x[:, c // 2:])]
+        rv.revnet_stack_fwd(r.desc, 2, *X, r.params, *X, r.ws)
+        torch.cuda.synchronize()
+        got.append(np.concatenate([t.cpu().numpy() for t in X], 1))
+    np.testing.assert_array_equal(got[0], got[1])
