@@ -58,7 +58,7 @@ struct Plan {
     size_t counters;      // ticket counters of the cross-workgroup reductions (ints)
     int n_counters;
     size_t bn_scratch;    // partial sums of the per-channel reductions
-    size_t wgrad_scratch; // partial filter gradients (backward only)
+    size_t wgrad_scratch, wgrad_floats; // partial filter gradients (backward only)
     size_t conv_scratch;  // partial tiles of channel-split convolutions (kept apart: a filter gradient's
                           // partial results stay alive across the following data-gradient convolution)
     size_t h[2];          // h_l = conv_l(a_l), fp32, input of layer l+1
@@ -85,6 +85,7 @@ struct Bufs {
     float *g[2];
     float *bn_scratch;
     float *wgrad_scratch, *conv_scratch;
+    size_t wgrad_floats;
     int *counters;
     uint16_t *wq_f[3], *wq_b[3];  // null where the layer does not use converted filters
     float *xf, *fout;

@@ -68,7 +68,7 @@ struct DownPlan {
     size_t stats[3];
     size_t counters;
     int n_counters;
-    size_t bn_scratch, wgrad_scratch, conv_scratch;
+    size_t bn_scratch, wgrad_scratch, wgrad_floats, conv_scratch;
     size_t wq_f[4], wq_b[4];  // bf16 filters (forward / data gradient); [kShortcut]: the shortcut
     bool bf16;
     size_t xs;     // x at the even positions, [n][c_in][h/2][w/2]
@@ -118,6 +118,7 @@ DownPlan make_down_plan(const rvn_down_desc &d, const Geo &full, bool backward) 
     p.bn_scratch = off;
     off = align_up(off + bn_s * 4);
     p.wgrad_scratch = off;
+    p.wgrad_floats = wg_s;
     off = align_up(off + wg_s * 4);
     p.conv_scratch = off;
     off = align_up(off + cv_s * 4);
@@ -147,6 +148,7 @@ DownPlan make_down_plan(const rvn_down_desc &d, const Geo &full, bool backward) 
 struct DownBufs {
     float *stats[3], *h[2], *g[2];
     float *bn_scratch, *wgrad_scratch, *conv_scratch, *xs, *hfull, *t;
+    size_t wgrad_floats;
     int *counters;
     uint16_t *wq_f[4], *wq_b[4];
 };
@@ -166,6 +168,7 @@ DownBufs bind(const DownPlan &p, void *ws, bool backward) {
     }
     o.bn_scratch = f(p.bn_scratch);
     o.wgrad_scratch = f(p.wgrad_scratch);
+    o.wgrad_floats = p.wgrad_floats;
     o.conv_scratch = f(p.conv_scratch);
     o.xs = f(p.xs);
     o.hfull = f(p.hfull);
@@ -263,7 +266,7 @@ void down_backward(Ctx &cx, const rvn_down_desc &d, const DownPlan &pl, const Do
                                       gr.d_shortcut_w, accumulate, b.t, b.conv_scratch, &sred)) {
                 wgrad_reduce(cx, sred);
             } else {
-                conv_wgrad(cx, xs, scale_shift, d.conv_dtype, dy, d.c_in, d.c_out, 1, pl.low, b.wgrad_scratch,
+                conv_wgrad(cx, xs, scale_shift, d.conv_dtype, dy, d.c_in, d.c_out, 1, pl.low, b.wgrad_scratch, b.wgrad_floats,
                            gr.d_shortcut_w, accumulate);
                 conv_dgrad(cx, dy, d.conv_dtype, p.shortcut_w, b.wq_b[kShortcut], d.c_in, d.c_out, 1, pl.low, b.t,
                            b.conv_scratch);
@@ -273,8 +276,8 @@ void down_backward(Ctx &cx, const rvn_down_desc &d, const DownPlan &pl, const Do
         if (d.conv_dtype != RVN_BF16 ||
             !conv_dgrad_wgrad_bf16(cx, xl, scale_shift, dcur, nullptr, b.wq_b[l], ly.cin, ly.cout, ly.ks, g, b.wgrad_scratch,
                                    gr.R.d_conv_w[l], accumulate, da, b.conv_scratch, &red)) {
-            conv_wgrad(cx, xl, scale_shift, d.conv_dtype, dcur, ly.cin, ly.cout, ly.ks, g, b.wgrad_scratch, gr.R.d_conv_w[l],
-                       accumulate, &red);
+            conv_wgrad(cx, xl, scale_shift, d.conv_dtype, dcur, ly.cin, ly.cout, ly.ks, g, b.wgrad_scratch, b.wgrad_floats,
+                       gr.R.d_conv_w[l], accumulate, &red);
             conv_dgrad(cx, dcur, d.conv_dtype, p.R.conv_w[l], b.wq_b[l], ly.cin, ly.cout, ly.ks, g, da, b.conv_scratch);
         }
         if (l == 0) upsample2_add(cx, b.t, d.c_in, pl.full, da);

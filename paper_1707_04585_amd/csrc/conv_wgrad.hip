@@ -109,12 +109,11 @@ WgradPlan plan_wgrad(int cin, int cout, int ks, const Geo &g) {
 
 size_t wgrad_scratch_floats(int cin, int cout, int ks, const Geo &g) {
     const WgradPlan w = plan_wgrad(cin, cout, ks, g);
-    const size_t a = w.ok ? std::max((size_t)w.S * w.part_stride, wgrad_gemm_f32_scratch_floats(cin, cout, ks, g)) : 0;
-    return std::max(a, wgrad_bf16_scratch_floats(cin, cout, ks, g));
+    return std::max(w.ok ? (size_t)w.S * w.part_stride : 0, wgrad_bf16_scratch_floats(cin, cout, ks, g));
 }
 
 void conv_wgrad(Ctx &cx, View x, const float *scale_shift, rvn_dtype dt, View dh, int cin, int cout,
-                int ks, Geo g, float *scratch, float *dw, bool accumulate, WgradReduce *defer) {
+                int ks, Geo g, float *scratch, size_t scratch_floats, float *dw, bool accumulate, WgradReduce *defer) {
     if (defer) defer->blocks = 0;
     const double P = (double)g.pixels();
     const double flops = 2.0 * P * cin * cout * ks * ks;
@@ -126,7 +125,7 @@ void conv_wgrad(Ctx &cx, View x, const float *scale_shift, rvn_dtype dt, View dh
         return;
     // (rows too wide for the row-band plan are refused whichever kernel would take them)
     if (dt == RVN_F32 && plan_wgrad(cin, cout, ks, g).ok &&
-        conv_wgrad_gemm_f32(cx, x, scale_shift, dh, cin, cout, ks, g, scratch, dw, accumulate,
+        conv_wgrad_gemm_f32(cx, x, scale_shift, dh, cin, cout, ks, g, scratch, scratch_floats, dw, accumulate,
                             P * cin * 4.0 + P * cout * 4.0, flops, defer))
         return;
     WgradLaunch L;

@@ -13,8 +13,8 @@
 // accumulators) and the workgroup's four wavefronts share the tile and split the pixels, which costs no
 // partial results in memory; a 1x1 wavefront holds 2x2 tiles, because with one tap the words staged per
 // flop would otherwise exceed what the last-level cache delivers.  Slices of the pixels go to further
-// workgroups until two are resident per compute unit; their partial results are summed by
-// wgrad_reduce_body in a fixed order (no floating-point atomics).
+// workgroups until two are resident per compute unit, or as many as the caller's scratch has room for;
+// their partial results are summed by wgrad_reduce_body in a fixed order (no floating-point atomics).
 //
 // Measured (mean over the layers of the four-stage bottleneck network, 16 images; the row-band kernel
 // before): 1x1 95 -> 32 us, 3x3 111 -> 61 us; 28 -> 28 3x3 at 19x21, 51 images: 21.7 -> 15.5 us.
@@ -226,7 +226,7 @@ struct WgemmPlan {
     bool ok;
 };
 
-WgemmPlan plan(int cin, int cout, int ks, const Geo &g) {
+WgemmPlan plan(int cin, int cout, int ks, const Geo &g, size_t scratch_floats) {
     WgemmPlan w{};
     const int seg = ks == 3 ? (kChunk + 2 * g.w + 2 + 63) / 64 : 1;
     if (seg > 4) return w;  // rows too wide for the staged runs
@@ -256,6 +256,11 @@ WgemmPlan plan(int cin, int cout, int ks, const Geo &g) {
     w.chunks = (int)((g.pixels() + kChunk - 1) / kChunk);
     int s = std::max(1, 512 / w.groups);  // two workgroups per compute unit
     s = std::min(s, std::max(1, w.chunks / 2));
+    // The scratch is sized for the row-band and bf16 kernels.  One partial result of the row-band kernel is as
+    // large as one of these (the tile chosen above pads no more than 32x32 does), so one always fits; fewer
+    // than wished fit only for a few pixels or rows of up to three (33 -> 263 channels, 70 images of 8x2).
+    s = (int)std::min<size_t>(s, scratch_floats / (size_t)w.part_stride);
+    if (s < 1) return w;
     w.per_slice = (w.chunks + s - 1) / s;
     w.slices = (w.chunks + w.per_slice - 1) / w.per_slice;
     w.ok = true;
@@ -272,17 +277,13 @@ uint32_t magic(int d) { return d == 1 ? 0u : (uint32_t)((1ull << 32) / (uint64_t
 
 }  // namespace
 
-size_t wgrad_gemm_f32_scratch_floats(int cin, int cout, int ks, const Geo &g) {
-    const WgemmPlan w = plan(cin, cout, ks, g);
-    return w.ok ? (size_t)w.slices * w.part_stride : 0;
-}
-
 bool conv_wgrad_gemm_f32(Ctx &cx, View x, const float *scale_shift, View dh, int cin, int cout, int ks, Geo g,
-                         float *scratch, float *dw, bool accumulate, double bytes, double flops, WgradReduce *defer) {
+                         float *scratch, size_t scratch_floats, float *dw, bool accumulate, double bytes, double flops,
+                         WgradReduce *defer) {
     const int64_t lim = (int64_t)1 << 30;  // element offsets are 32-bit byte offsets
     auto fits = [&](const View &v, int c) { return (int64_t)g.n * v.sn + (int64_t)c * v.sc + (int64_t)g.h * g.w < lim; };
     if (!fits(x, cin) || !fits(dh, cout)) return false;
-    const WgemmPlan w = plan(cin, cout, ks, g);
+    const WgemmPlan w = plan(cin, cout, ks, g, scratch_floats);
     if (!w.ok) return false;
     WgradReduce red{};
     red.part = scratch; red.dw = dw;

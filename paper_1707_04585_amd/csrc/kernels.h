@@ -279,9 +279,10 @@ void conv_dgrad(Ctx &cx, View dh, rvn_dtype dt, const float *w, const uint16_t *
 // a(x) = max(x*scale + shift, 0) formed on the fly from the layer input x as in
 // conv_fwd; with dt == RVN_BF16 a and dh are rounded to bf16 before multiplying.
 // With `defer` the ordered sum of the partial results is not launched but
-// described in *defer for the caller to run (before `scratch` is reused).
-void conv_wgrad(Ctx &cx, View x, const float *scale_shift, rvn_dtype dt, View dh, int cin, int cout,
-                int ks, Geo g, float *scratch, float *dw, bool accumulate, WgradReduce *defer = nullptr);
+// described in *defer for the caller to run (before `scratch` is reused).  scratch_floats: what there is of
+// scratch, at least wgrad_scratch_floats(...).
+void conv_wgrad(Ctx &cx, View x, const float *scale_shift, rvn_dtype dt, View dh, int cin, int cout, int ks, Geo g,
+                float *scratch, size_t scratch_floats, float *dw, bool accumulate, WgradReduce *defer = nullptr);
 void wgrad_reduce(Ctx &cx, const WgradReduce &r);
 
 // True while the environment variable RVN_SEPARATE_LAUNCHES is "1": the data gradient and the filter
@@ -316,10 +317,10 @@ bool conv_wgrad_bf16(Ctx &cx, View x, const float *scale_shift, View dh, int cin
                      float *scratch, float *dw, bool accumulate, double bytes, double flops, WgradReduce *defer);
 
 // The filter gradient with fp32 operands as a tiled matrix product over the flat pixel index
-// (conv_wgrad_gemm_f32.hip); the contract of conv_wgrad_bf16, scratch of wgrad_gemm_f32_scratch_floats(...) floats.
-size_t wgrad_gemm_f32_scratch_floats(int cin, int cout, int ks, const Geo &g);
+// (conv_wgrad_gemm_f32.hip); the contract of conv_wgrad_bf16, with as many partial results as scratch_floats hold.
 bool conv_wgrad_gemm_f32(Ctx &cx, View x, const float *scale_shift, View dh, int cin, int cout, int ks, Geo g,
-                         float *scratch, float *dw, bool accumulate, double bytes, double flops, WgradReduce *defer);
+                         float *scratch, size_t scratch_floats, float *dw, bool accumulate, double bytes, double flops,
+                         WgradReduce *defer);
 
 // ---- fixed-point residual stream (Section 3.2, "Numerical error") ------------
 // A stream element is an int32 code q standing for q * 2^-frac_bits; the Views

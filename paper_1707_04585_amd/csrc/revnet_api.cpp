@@ -123,6 +123,7 @@ Plan make_plan(const rvn_block_desc &d, const Geo &g, bool backward, bool fixed)
     p.bn_scratch = off;
     off = align_up(off + bn_s * 4);
     p.wgrad_scratch = off;
+    p.wgrad_floats = wg_s;
     off = align_up(off + wg_s * 4);
     p.conv_scratch = off;
     off = align_up(off + cv_s * 4);
@@ -190,6 +191,7 @@ Bufs bind(const Plan &p, void *ws) {
     o.bn_scratch = reinterpret_cast<float *>(b + p.bn_scratch);
     o.counters = reinterpret_cast<int *>(b + p.counters);
     o.wgrad_scratch = reinterpret_cast<float *>(b + p.wgrad_scratch);
+    o.wgrad_floats = p.wgrad_floats;
     o.conv_scratch = reinterpret_cast<float *>(b + p.conv_scratch);
     o.xf = reinterpret_cast<float *>(b + p.xf);
     o.fout = reinterpret_cast<float *>(b + p.fout);
@@ -405,7 +407,7 @@ void func_backward(Ctx &cx, const rvn_block_desc &d, const Plan &pl, const Bufs 
                 cx.fail(hipErrorInvalidValue);
                 return;
             }
-            conv_wgrad(cx, xl, st + 2 * ly.cin, d.conv_dtype, dh, ly.cin, ly.cout, ly.ks, g, b.wgrad_scratch,
+            conv_wgrad(cx, xl, st + 2 * ly.cin, d.conv_dtype, dh, ly.cin, ly.cout, ly.ks, g, b.wgrad_scratch, b.wgrad_floats,
                        gr.d_conv_w[l], accumulate, &red);
             conv_dgrad(cx, dh, d.conv_dtype, p.conv_w[l], b.wq_b[l], ly.cin, ly.cout, ly.ks, g, da, b.conv_scratch);
         }

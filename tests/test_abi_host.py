@@ -151,6 +151,17 @@ def test_workspace_does_not_depend_on_depth_and_scales_with_batch():
     assert abs(c50[1]["algorithmic_bytes"] - (c1[1]["algorithmic_bytes"] + 49 * per_block_bytes)) < 1e-6 * c50[1]["algorithmic_bytes"]
 
 
+@pytest.mark.parametrize("kind,conv,c_half,width,n,h,w,fwd,bwd", [
+    ("basic", "bf16", 390, 0, 23, 15, 3, 8055552, 23019264),
+    ("bottleneck", "bf16", 3, 413, 26, 7, 3, 5849856, 16976896),
+    ("bottleneck", "f32", 33, 263, 70, 8, 2, 2413312, 13728000),
+    ("basic", "f32", 48, 0, 48, 2, 69, 1290752, 10912256),
+])
+def test_workspace_sizes_are_kept(kind, conv, c_half, width, n, h, w, fwd, bwd):
+    """Sizes that callers may have stored: a kernel added later lives in the room that was there."""
+    assert rv.revnet_workspace_bytes(rv.BlockDesc(kind, c_half, width, conv_dtype=conv), n, h, w) == (fwd, bwd)
+
+
 @pytest.mark.parametrize("kind,c,width", [("basic", 66, 0), ("bottleneck", 136, 34)])
 def test_ragged_bf16_layers_take_their_statistics_from_a_pass_over_the_tensor(kind, c, width):
     """bf16 channel counts off the 8- and 16-channel steps: 32 rows cut into whole tiles and 31 do not, and the bytes

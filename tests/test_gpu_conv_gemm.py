@@ -26,6 +26,9 @@ CASES = [
     dict(kind="bottleneck", n=16, c=384, h=14, w=14, width=40),   # several tiles of channels, chunks and slices
     dict(kind="bottleneck", n=40, c=256, h=28, w=28, width=72),   # large tiles, ragged channels
     dict(kind="bottleneck", n=2, c=1100, h=7, w=5, width=520),    # filters larger than the activations
+    # fewer partial filter gradients fit the scratch than would fill the chip
+    dict(kind="bottleneck", n=70, c=66, h=8, w=2, width=263),
+    dict(kind="basic", n=48, c=96, h=2, w=69),
 ]
 
 
