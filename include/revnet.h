@@ -228,8 +228,7 @@ int revnet_stack_bwd(const rvn_block_desc *desc, int32_t depth,
  * and frees nothing, on the device or through any library.
  * Limit: shapes whose forward workspace (revnet_workspace_bytes: fwd_bytes)
  * exceeds RVN_STATIC_WS_BYTES are rejected with RVN_ERR_WORKSPACE before
- * anything is enqueued.  (The bf16 copies of small 1x1 filters, at most 128 KiB
- * of fwd_bytes, lie behind the array and do not count.)
+ * anything is enqueued.
  * Sharing: every call on one GPU uses that GPU's one array, on whatever
  * stream.  Calls on the same stream are ordered and safe; calls whose work
  * can overlap on one GPU (different streams, different host threads without

@@ -49,7 +49,6 @@ View view_of(const rvn_tensor *t);
 struct Layer {
     int cin, cout, ks;
 };
-constexpr size_t kSmallPrepBytes = 128 << 10;  // bound on Plan::small_prep of a forward plan
 // Workspace layout.  Offsets in bytes from the workspace base.
 struct Plan {
     int L;
@@ -63,16 +62,13 @@ struct Plan {
                           // partial results stay alive across the following data-gradient convolution)
     size_t h[2];          // h_l = conv_l(a_l), fp32, input of layer l+1
     size_t g[2];          // gradient ping-pong buffers (backward only)
-    // bf16 convolutions with large filters: the filters of the function at hand
-    // in bf16 and K order, for the forward convolution and (backward only) for
-    // the data gradient; `prep[l]` says whether layer l uses them
+    // bf16 convolutions: the filters of the function at hand in bf16 and K order, for
+    // the forward convolution and (backward only) for the data gradient; 0 where layer l has none
     size_t wq_f[3], wq_b[3];
-    bool prep[3];
-    size_t small_prep;  // bytes of the forward copies that are there only for the speed of small layers
     // fixed-point residual stream only: the function's input as fp32 and the
     // function's value before it is rounded into the stream
     size_t xf, fout;
-    // per-tile statistics that a 1x1 bf16 convolution leaves for the BN layer reading its output
+    // per-tile statistics that a convolution leaves for the BN layer reading its output
     size_t emit, emit_floats;
     // two spare layer-0 statistics arrays: a function's input statistics that a launch of the
     // backward pass computed ahead (merge of the producing convolution's partial results)

@@ -76,9 +76,7 @@ bool wants_prep(const rvn_block_desc &d, const Layer &ly, const Geo &g) {
 }
 
 // Smaller filters of other channel counts, for the sake of the kernels that read prepared filters; 1x1 up to
-// the usual reduction to a quarter (beyond it the padded copy grows past what the filter is worth).  At
-// most kSmallPrepBytes of forward copies per function: filters of fewer than 16384 elements, padded to 32 rows
-// and 16 columns (1x1, two of them: 90112) or to 8 columns (3x3: 36288 each).
+// the usual reduction to a quarter (beyond it the padded copy grows past what the filter is worth).
 bool wants_small_prep(const rvn_block_desc &d, const Layer &ly, const Geo &g) {
     if (d.conv_dtype != RVN_BF16) return false;
     if (ly.ks == 3) return conv3x3_bf16_ok(ly.cin, ly.cout, g) || conv3x3_bf16_ok(ly.cout, ly.cin, g);
@@ -106,12 +104,9 @@ Plan make_plan(const rvn_block_desc &d, const Geo &g, bool backward, bool fixed)
     }
     for (int l = 0; l < p.L; ++l) {
         const Layer &ly = p.layers[l];
-        const bool large = wants_prep(d, ly, g);
-        p.prep[l] = large || wants_small_prep(d, ly, g);
-        if (!p.prep[l]) continue;
+        if (!wants_prep(d, ly, g)) continue;
         p.wq_f[l] = off;
         off = align_up(off + filter_bf16_elems(ly.cout, ly.cin, ly.ks) * 2);
-        if (!large) p.small_prep += off - p.wq_f[l];
         if (backward) {
             p.wq_b[l] = off;
             off = align_up(off + filter_bf16_elems(ly.cin, ly.cout, ly.ks) * 2);
@@ -131,14 +126,31 @@ Plan make_plan(const rvn_block_desc &d, const Geo &g, bool backward, bool fixed)
         // (mean, M2) per channel and pixel tile of a convolution's output: 128-pixel tiles of the bf16
         // 1x1 kernel, 64-pixel wavefront shares of the 3x3 kernels
         const size_t tiles128 = ((size_t)g.n * (((size_t)g.h * g.w + 3) / 4) + 31) / 32, tiles64 = P / 64 + kAlign;
+        size_t used = 0;  // what a bf16 kernel can write: whole tiles only, and nothing from ragged channel counts
         for (int l = 0; l < p.L; ++l) {
             const Layer &ly = p.layers[l];
             if (d.conv_dtype == RVN_BF16 && ly.ks == 1) p.emit_floats = std::max(p.emit_floats, (size_t)ly.cout * tiles128 * 2);
             if (ly.ks == 3 && (d.conv_dtype == RVN_BF16 || ly.cout <= 32))
                 p.emit_floats = std::max(p.emit_floats, (size_t)ly.cout * tiles64 * 2);
+            if (ly.cin % (ly.ks == 1 ? 16 : 8) == 0)
+                used = std::max(used, (size_t)ly.cout * (P / (ly.ks == 1 ? 128 : 64)) * 2);
         }
         p.emit = off;
         off = align_up(off + p.emit_floats * 4);
+        // The copies of smaller filters lie in what that buffer has to spare, so that they cost no workspace: all
+        // of it where every layer is ragged, else at least 2 KB per output channel of the 3x3 layers.  A copy that finds
+        // no room is not made, and its layer runs on the general kernel.
+        size_t at = p.emit + align_up(used * 4);
+        for (int pass = 0; pass < (backward ? 2 : 1); ++pass)
+            for (int l = 0; l < p.L; ++l) {
+                const Layer &ly = p.layers[l];
+                if (wants_prep(d, ly, g) || !wants_small_prep(d, ly, g)) continue;
+                const size_t bytes = align_up(filter_bf16_elems(pass ? ly.cin : ly.cout, pass ? ly.cout : ly.cin, ly.ks) * 2);
+                if (at + bytes > off) continue;
+                (pass ? p.wq_b : p.wq_f)[l] = at;
+                p.emit_floats = std::min(p.emit_floats, (at - p.emit) / 4);
+                at += bytes;
+            }
     }
     for (int i = 0; i < 2; ++i) {
         p.stats_in[i] = off;
@@ -181,8 +193,8 @@ Bufs bind(const Plan &p, void *ws) {
     Bufs o{};
     for (int l = 0; l < 3; ++l) {
         o.stats[l] = reinterpret_cast<float *>(b + p.stats[l]);
-        o.wq_f[l] = p.prep[l] ? reinterpret_cast<uint16_t *>(b + p.wq_f[l]) : nullptr;
-        o.wq_b[l] = p.prep[l] && p.wq_b[l] ? reinterpret_cast<uint16_t *>(b + p.wq_b[l]) : nullptr;
+        o.wq_f[l] = p.wq_f[l] ? reinterpret_cast<uint16_t *>(b + p.wq_f[l]) : nullptr;
+        o.wq_b[l] = p.wq_b[l] ? reinterpret_cast<uint16_t *>(b + p.wq_b[l]) : nullptr;
     }
     for (int l = 0; l < 2; ++l) {
         o.h[l] = reinterpret_cast<float *>(b + p.h[l]);

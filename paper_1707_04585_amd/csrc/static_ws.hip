@@ -12,14 +12,11 @@ namespace {
 
 constexpr size_t kStaticWsBytes = RVN_STATIC_WS_BYTES;  // what revnet_stack_fwd_static can plan into
 constexpr int kMaxDevices = 64;
-constexpr size_t kSmallPrepBytes = rvn::api::kSmallPrepBytes;
 
 // The workspace itself.  One copy per GPU that loads the library, held until
 // the process ends.  In host code this name is only a handle for
 // hipGetSymbolAddress; it is not a device address.
-// The filter copies of small layers lie beyond the stated size, so that they take no shape away from it.
-constexpr size_t kScratchBytes = kStaticWsBytes + kSmallPrepBytes;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kStaticWsBytes];
 
 std::mutex g_mu;
 void *g_scratch_ptr[kMaxDevices] = {};  // device address of `scratch` on each device, once looked up
@@ -64,7 +61,7 @@ int revnet_stack_fwd_static(const rvn_block_desc *desc, int32_t depth, const rvn
     if (!params) return fail(RVN_ERR_NULL, "params is NULL");
     for (int k = 0; k < depth; ++k)
         if (int rc = check_params(*desc, &params[k], "params")) return rc;
-    if (pl.total - pl.small_prep > kStaticWsBytes || pl.total > kScratchBytes)
+    if (pl.total > kStaticWsBytes)
         return fail(RVN_ERR_WORKSPACE,
                     "this shape needs a workspace of %zu bytes; the built-in workspace of revnet_stack_fwd_static holds "
                     "%zu (use revnet_stack_fwd with a workspace of the caller's)",
@@ -75,7 +72,7 @@ int revnet_stack_fwd_static(const rvn_block_desc *desc, int32_t depth, const rvn
     const rvn_tensor *t[4] = {x1, x2, y1, y2};
     const char *nm[4] = {"x1", "x2", "y1", "y2"};
     for (int i = 0; i < 4; ++i)
-        if (overlaps_range(t[i], ws, kScratchBytes)) return fail(RVN_ERR_ALIAS, "%s overlaps the built-in workspace", nm[i]);
+        if (overlaps_range(t[i], ws, kStaticWsBytes)) return fail(RVN_ERR_ALIAS, "%s overlaps the built-in workspace", nm[i]);
     Ctx cx;
     cx.stream = static_cast<hipStream_t>(hip_stream);
     // (stack_forward starts by clearing the ticket counters with a fill kernel: the array keeps

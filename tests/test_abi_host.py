@@ -156,6 +156,9 @@ def test_workspace_does_not_depend_on_depth_and_scales_with_batch():
     ("bottleneck", "bf16", 3, 413, 26, 7, 3, 5849856, 16976896),
     ("bottleneck", "f32", 33, 263, 70, 8, 2, 2413312, 13728000),
     ("basic", "f32", 48, 0, 48, 2, 69, 1290752, 10912256),
+    ("bottleneck", "bf16", 132, 66, 64, 56, 56, 107887104, 356190464),   # small filters of ragged channel counts
+    ("bottleneck", "bf16", 100, 44, 13, 27, 23, 3043840, 19125504),
+    ("basic", "bf16", 26, 0, 64, 32, 32, 7097600, 30166272),
 ])
 def test_workspace_sizes_are_kept(kind, conv, c_half, width, n, h, w, fwd, bwd):
     """Sizes that callers may have stored: a kernel added later lives in the room that was there."""

@@ -18,7 +18,11 @@ CASES = [
     dict(n=48, c=136, h=28, w=28, width=35),   # 3x3 on its own kernel: two octets and three channels past
     dict(kind="basic", n=132, c=26, h=16, w=16),   # 13 channels
     dict(kind="basic", n=70, c=90, h=15, w=14),    # 45 channels, rows of two pixels past whole 4-pixel groups
-    dict(n=40, c=130, h=28, w=28, width=36),   # two output tiles per wavefront, statistics from the epilogue
+    dict(n=40, c=130, h=28, w=28, width=36),   # two output tiles per wavefront
+    dict(n=48, c=136, h=20, w=20, width=17),   # a reduction to a quarter
+    dict(n=2, c=464, h=14, w=14, width=58),    # the data gradient's filter copies find no room
+    dict(n=40, c=192, h=20, w=20, width=52),   # whole steps into ragged ones: statistics beside the filter copies
+    dict(kind="basic", n=91, c=66, h=31, w=31),
 ]
 
 
