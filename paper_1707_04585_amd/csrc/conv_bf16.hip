@@ -132,35 +132,39 @@ __global__ __launch_bounds__(kThreads) void conv_bf16_k(const Bf16Args p) {
             const int lr = t % p.lrows, img = t / p.lrows;
             const int n = n0 + img, row = row0 - PAD + lr, col = qx * 4, chb = c0 + oc * 8;
             const bool live = n < N && row >= 0 && row < H;
-            // Every load is issued, from a clamped address where the item leaves the tensor, and selected
-            // afterwards: a load behind a lane's own condition is waited for before the next is issued.
+            // All loads of an item are issued together, from a clamped address where a channel or a pixel lies
+            // past the end, and selected afterwards: a load behind a condition of its own is waited for
+            // before the next is issued.  An item with nothing to load skips them as a whole.
             float v[8][4], sc[8], sh[8];
-            const float *const src0 = p.in + (live ? (int64_t)n * p.isn + row * W + col : 0);
-            const int d1 = live ? min(col + 1, W - 1) - col : 0, d2 = live ? min(col + 2, W - 1) - col : 0;
-            const int d3 = live ? min(col + 3, W - 1) - col : 0;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int ch = min(chb + k, CI - 1);
-                const float *src = src0 + (int64_t)ch * p.isc;
-                if (vec) {
-                    const float4 q = *reinterpret_cast<const float4 *>(src);
-                    v[k][0] = q.x; v[k][1] = q.y; v[k][2] = q.z; v[k][3] = q.w;
-                } else {
-                    v[k][0] = src[0]; v[k][1] = src[d1]; v[k][2] = src[d2]; v[k][3] = src[d3];
-                }
-                if (p.scale_shift) {
-                    sc[k] = p.scale_shift[ch];
-                    sh[k] = p.scale_shift[CI + ch];
-                }
-            }
+            for (int k = 0; k < 8; ++k)
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const bool in = live && chb + k < CI;
+                for (int j = 0; j < 4; ++j) v[k][j] = 0.f;
+            if (live && chb < CI) {
+                const float *const src0 = p.in + (int64_t)n * p.isn + row * W + col;
+                const int d1 = min(col + 1, W - 1) - col, d2 = min(col + 2, W - 1) - col, d3 = min(col + 3, W - 1) - col;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (p.scale_shift) v[k][j] = fmaxf(fmaf(v[k][j], sc[k], sh[k]), 0.f);
-                    v[k][j] = in ? v[k][j] : 0.f;
+                for (int k = 0; k < 8; ++k) {
+                    const int ch = min(chb + k, CI - 1);
+                    const float *src = src0 + (int64_t)ch * p.isc;
+                    if (vec) {
+                        const float4 q = *reinterpret_cast<const float4 *>(src);
+                        v[k][0] = q.x; v[k][1] = q.y; v[k][2] = q.z; v[k][3] = q.w;
+                    } else {
+                        v[k][0] = src[0]; v[k][1] = src[d1]; v[k][2] = src[d2]; v[k][3] = src[d3];
+                    }
+                    if (p.scale_shift) {
+                        sc[k] = p.scale_shift[ch];
+                        sh[k] = p.scale_shift[CI + ch];
+                    }
                 }
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if (p.scale_shift) v[k][j] = fmaxf(fmaf(v[k][j], sc[k], sh[k]), 0.f);
+                        v[k][j] = chb + k < CI ? v[k][j] : 0.f;
+                    }
             }
             uint16_t *dst = in_lds + ((img * p.lrows + lr) * p.lcols + PAD + col) * REC + oc * 8;
 #pragma unroll
@@ -201,12 +205,16 @@ __global__ __launch_bounds__(kThreads) void conv_bf16_k(const Bf16Args p) {
                 const int ko = co0 + kol, chb = c0 + oc * 8;
                 float v[8];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {  // (every load issued, as above)
-                    const int ch = min(chb + k, CI - 1), kc = min(ko, CO - 1);
-                    v[k] = p.w[p.transposed ? ((int64_t)ch * CO + kc) * KS2 + (KS2 - 1 - tap) : ((int64_t)kc * CI + ch) * KS2 + tap];
-                }
+                for (int k = 0; k < 8; ++k) v[k] = 0.f;
+                if (ko < CO && chb < CI) {  // (as above)
 #pragma unroll
-                for (int k = 0; k < 8; ++k) v[k] = ko < CO && chb + k < CI ? v[k] : 0.f;
+                    for (int k = 0; k < 8; ++k) {
+                        const int ch = min(chb + k, CI - 1);
+                        v[k] = p.w[p.transposed ? ((int64_t)ch * CO + ko) * KS2 + (KS2 - 1 - tap) : ((int64_t)ko * CI + ch) * KS2 + tap];
+                    }
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) v[k] = chb + k < CI ? v[k] : 0.f;
+                }
                 uint4 rec;
                 rec.x = pack2(v[0], v[1]);
                 rec.y = pack2(v[2], v[3]);
