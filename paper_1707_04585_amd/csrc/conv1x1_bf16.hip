@@ -64,11 +64,12 @@ size_t operand_elems(int rows, int cols) { return (size_t)((rows + 31) / 32) * 3
 }  // namespace
 
 // Channel counts that are not whole 16-channel steps included: the last step is padded in registers
-// (RAGGED).  Two blocks of 132 + 132 channels, 64 images of 56x56: 6.26 ms with the staged kernel of
-// conv_bf16.hip for these layers, 4.76 ms with this one; 516 + 516 at 14x14: 6.14 and 2.63 ms.  Below 16
-// channels half of a step or more would be padding.
-bool conv1x1_direct_ok(int k_channels, const Geo &g) {
-    return k_channels >= 16 && (int64_t)g.h * g.w >= 4 && (int64_t)g.n * ((g.h * g.w + 3) / 4) < (1 << 30);
+// (RAGGED).  A training step of two blocks of 132 + 132 channels reduced to 66, 64 images of 56x56: 6.61 ms with
+// the staged kernel of conv_bf16.hip for the 1x1 layers, 4.32 ms with this one; 516 + 516 reduced to 258, 64 of 7x7:
+// 2.75 and 1.63 ms.  Below 16 channels half of a step or more would be padding.
+bool conv1x1_direct_ok(int ci, int co, const Geo &g) {
+    return ci >= 16 && (int64_t)g.h * g.w >= 4 && (int64_t)g.n * ((g.h * g.w + 3) / 4) < (1 << 30) &&
+           !conv1x1_staged_better(ci, co, g);
 }
 
 size_t filter_1x1_elems(int rows, int k_channels) { return operand_elems(rows, k_channels); }
@@ -136,14 +137,14 @@ int images_per_launch(View in, const View *r, View out, int ci, int co, Geo g) {
 bool conv1x1_bf16_plan(View in, const float *scale_shift, const uint16_t *wq, int ci, int co, Geo g, Epilogue ep,
                        const View *r, View out, C1Launch &L) {
     // (the shared launches have no instance for a last step of fewer than 16 channels)
-    if (!wq || ci % 16 != 0 || !conv1x1_direct_ok(ci, g) || images_per_launch(in, r, out, ci, co, g) < g.n) return false;
+    if (!wq || ci % 16 != 0 || !conv1x1_direct_ok(ci, co, g) || images_per_launch(in, r, out, ci, co, g) < g.n) return false;
     L = plan_slice(in, scale_shift, wq, ci, co, g, ep, r, out, 0, g.n);
     return true;
 }
 
 bool conv1x1_bf16(Ctx &cx, View in, const float *scale_shift, const uint16_t *wq, int ci, int co, Geo g,
                   Epilogue ep, const View *r, View out) {
-    if (!wq || !conv1x1_direct_ok(ci, g)) return false;
+    if (!wq || !conv1x1_direct_ok(ci, co, g)) return false;
     const int slice_n = images_per_launch(in, r, out, ci, co, g);
     if (slice_n == 0) {  // one image alone is too large
         if (ci % 16 != 0) return false;

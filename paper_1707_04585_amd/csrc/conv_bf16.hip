@@ -339,6 +339,20 @@ __global__ __launch_bounds__(kThreads) void prep_filter_k(const PrepArgs p) { pr
 
 }  // namespace
 
+// Ragged 1x1 layers that the staged kernel of this file does better than the register-operand one of
+// conv1x1_bf16.hip: one round trip for all channels (a chunk of up to 64) instead of a chain of 16-channel steps,
+// where the layer is small enough for one pixel group per wavefront.  Staged / register-operand kernel, us: 26 -> 52
+// channels, 32 images of 14x14 6.4 / 7.9; 52 -> 26, one of 28x28 7.0 / 9.0; 34 -> 68, 16 of 21x21 8.2 / 10.2.  The
+// other side of each line: 100 -> 50 (chunk of 128), 8 of 28x28 14.7 / 14.7, 68 -> 34, 4 of 14x14 11.9 / 10.7; 400
+// tiles or more, 60 -> 30, 32 of 40x40 12.8 / 11.1; four groups per wavefront, 50 -> 100, 8 of 7x7 29.8 / 11.4.
+bool conv1x1_staged_better(int ci, int co, const Geo &g) {
+    if (ci % 16 == 0 || ci > 64) return false;
+    const int64_t groups = (int64_t)g.n * ((g.h * g.w + 3) / 4);
+    if ((groups + 31) / 32 * ((co + 31) / 32) > 256) return false;
+    const Bf16Plan pl = plan_bf16(ci, co, 1, g);
+    return pl.ok && pl.MT == 1 && pl.NT == 1 && pl.KC >= ci;
+}
+
 size_t conv_bf16_scratch_floats(int ci, int co, int ks, const Geo &g) {
     return ks == 3 ? conv3x3_bf16_scratch_floats(ci, co, g) : 0;
 }
@@ -365,13 +379,13 @@ PrepArgs plan_filter_prep(const FilterPrep *f, int count, Geo g, double *bytes_o
         bytes += 4.0 * fp.cin * fp.cout * fp.ks * fp.ks;
         const int cip = (fp.cin + 7) / 8 * 8, cop = (fp.cout + 7) / 8 * 8, ks2 = fp.ks * fp.ks;
         if (fp.qf) {
-            if (fp.ks == 1 && conv1x1_direct_ok(fp.cin, g))
+            if (fp.ks == 1 && conv1x1_direct_ok(fp.cin, fp.cout, g))
                 add(fp, fp.qf, 2, (fp.cin + 15) / 16, (int64_t)filter_1x1_elems(fp.cout, fp.cin));
             else
                 add(fp, fp.qf, 0, cip, (int64_t)fp.cout * cip);
         }
         if (fp.qb) {
-            if (fp.ks == 1 && conv1x1_direct_ok(fp.cout, g))
+            if (fp.ks == 1 && conv1x1_direct_ok(fp.cout, fp.cin, g))
                 add(fp, fp.qb, 3, (fp.cout + 15) / 16, (int64_t)filter_1x1_elems(fp.cin, fp.cout));
             else
                 add(fp, fp.qb, 1, cop, (int64_t)fp.cin * cop);
@@ -390,7 +404,7 @@ void prep_filters_bf16(Ctx &cx, const PrepArgs &a, double bytes) {
 
 bool conv_bf16(Ctx &cx, View in, const float *scale_shift, const float *w, const uint16_t *wq, bool transposed,
                int ci, int co, int ks, Geo g, Epilogue ep, const View *r, View out, float *scratch) {
-    if (ks == 1 && wq && conv1x1_direct_ok(ci, g)) {
+    if (ks == 1 && wq && conv1x1_direct_ok(ci, co, g)) {
         if (conv1x1_bf16(cx, in, scale_shift, wq, ci, co, g, ep, r, out)) return true;
         wq = nullptr;  // ragged channels with images of 4 GiB or more: 64-bit offsets below, filter in its own layout
     }

@@ -76,7 +76,7 @@ struct EmittedStats {
 // such a buffer.
 //
 // 1x1 filters whose reduction length (cin forward, cout for the data gradient)
-// passes conv1x1_direct_ok are stored instead in the operand order of
+// passes conv1x1_direct_ok (with the other count as output channels) are stored instead in the operand order of
 // conv1x1_bf16: [rows / 32][k_channels / 16][64 lanes][8], zero padded.
 size_t filter_bf16_elems(int rows, int k_channels, int ks);
 struct FilterPrep {
@@ -263,9 +263,10 @@ void prep_filters_bf16(Ctx &cx, const PrepArgs &a, double bytes);
 
 // 1x1 convolution without LDS: activations go from HBM to the matrix
 // instruction's registers directly.  Needs the filter in operand order (wq from
-// prep_filters_bf16) and conv1x1_direct_ok(ci, g); returns false (nothing
+// prep_filters_bf16) and conv1x1_direct_ok(ci, co, g); returns false (nothing
 // launched) otherwise.
-bool conv1x1_direct_ok(int k_channels, const Geo &g);
+bool conv1x1_direct_ok(int ci, int co, const Geo &g);
+bool conv1x1_staged_better(int ci, int co, const Geo &g);
 size_t filter_1x1_elems(int rows, int k_channels);
 bool conv1x1_bf16(Ctx &cx, View in, const float *scale_shift, const uint16_t *wq, int ci, int co, Geo g,
                   Epilogue ep, const View *r, View out);

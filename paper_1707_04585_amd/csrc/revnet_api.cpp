@@ -68,8 +68,8 @@ int check_geo(int64_t n, int64_t h, int64_t w) {
 // every workgroup of the convolution.
 bool wants_prep(const rvn_block_desc &d, const Layer &ly, const Geo &g) {
     if (d.conv_dtype != RVN_BF16) return false;
-    auto whole_steps = [&](int k) { return k % 16 == 0 && conv1x1_direct_ok(k, g); };
-    if (ly.ks == 1 && (whole_steps(ly.cin) || whole_steps(ly.cout))) return true;
+    auto whole_steps = [&](int ci, int co) { return ci % 16 == 0 && conv1x1_direct_ok(ci, co, g); };
+    if (ly.ks == 1 && (whole_steps(ly.cin, ly.cout) || whole_steps(ly.cout, ly.cin))) return true;
     auto whole_octets = [&](int ci, int co) { return ci % 8 == 0 && conv3x3_bf16_ok(ci, co, g); };
     if (ly.ks == 3 && (whole_octets(ly.cin, ly.cout) || whole_octets(ly.cout, ly.cin))) return true;
     return (int64_t)ly.cin * ly.cout * ly.ks * ly.ks >= 16384;
@@ -81,7 +81,7 @@ bool wants_small_prep(const rvn_block_desc &d, const Layer &ly, const Geo &g) {
     if (d.conv_dtype != RVN_BF16) return false;
     if (ly.ks == 3) return conv3x3_bf16_ok(ly.cin, ly.cout, g) || conv3x3_bf16_ok(ly.cout, ly.cin, g);
     return std::max(ly.cin, ly.cout) <= 4 * std::min(ly.cin, ly.cout) &&
-           (conv1x1_direct_ok(ly.cin, g) || conv1x1_direct_ok(ly.cout, g));
+           (conv1x1_direct_ok(ly.cin, ly.cout, g) || conv1x1_direct_ok(ly.cout, ly.cin, g));
 }
 
 Plan make_plan(const rvn_block_desc &d, const Geo &g, bool backward, bool fixed) {
