@@ -348,7 +348,7 @@ bool launch_shape(Ctx &cx, const GemmArgs &a, int shape, Plane pl, dim3 grid) {
         case 1: return launch_if<1, 2, 160>(cx, a, pl, grid) || launch_if<1, 4, 288>(cx, a, pl, grid);
         case 2: return launch_if<2, 4, 288>(cx, a, pl, grid);
         case 3: return launch_if<3, 2, 160>(cx, a, pl, grid) || launch_if<3, 4, 288>(cx, a, pl, grid);
-        case 4: return launch_if<4, 1, 96>(cx, a, pl, grid) || launch_if<4, 2, 160>(cx, a, pl, grid) || launch_if<4, 4, 288>(cx, a, pl, grid);
+        case 4: return launch_if<4, 4, 288>(cx, a, pl, grid);  // (shorter rows: shape 3, 6 or 7)
         case 5: return launch_if<5, 4, 160>(cx, a, pl, grid);
         case 6: return launch_if<6, 2, 160>(cx, a, pl, grid) || launch_if<6, 4, 160>(cx, a, pl, grid);
         case 7: return launch_if<7, 1, 96>(cx, a, pl, grid) || launch_if<7, 2, 160>(cx, a, pl, grid) || launch_if<7, 4, 160>(cx, a, pl, grid);
@@ -363,14 +363,25 @@ bool launch_shape(Ctx &cx, const GemmArgs &a, int shape, Plane pl, dim3 grid) {
 
 uint32_t magic(int d) { return d == 1 ? 0u : (uint32_t)((1ull << 32) / (uint64_t)d); }
 
+// Fewer than 17 channels would leave half of a 32-row tile idle, and up to 32 channels in rows of whole
+// 4-pixel groups the row-band kernel also leaves the statistics of its output and shares a launch with
+// the filter gradient; above, and for every other row length, this kernel took a quarter to a half of its time.
+bool takes(int co, const Geo &g) { return co > 32 || (co > 16 && (g.w & 3) != 0); }
+
 }  // namespace
+
+// Which instance a layer of dense tensors runs on, for the tests: shape * 4096 + pieces * 512 + pitch, or -1 (another kernel).
+extern "C" int rvn_conv_gemm_f32_instance(int ci, int co, int ks, int n, int h, int w) {
+    const Geo g{n, h, w};
+    const int shape = takes(co, g) ? choose_shape(g, ci, co, ks) : -1;
+    if (shape < 0) return -1;
+    const Plane pl = plane_of(kShapes[shape], w);
+    return shape * 4096 + pl.seg * 512 + pl.pb;
+}
 
 bool conv_gemm_f32(Ctx &cx, View in, const float *scale_shift, const float *w, bool transposed, int ci, int co, int ks,
                    Geo g, Epilogue ep, const View *r, View out) {
-    // Fewer than 17 channels would leave half of a 32-row tile idle, and up to 32 channels in rows of whole
-    // 4-pixel groups the row-band kernel also leaves the statistics of its output and shares a launch with
-    // the filter gradient; above, and for every other row length, this kernel took a quarter to a half of its time.
-    if (co <= 16 || (co <= 32 && (g.w & 3) == 0)) return false;
+    if (!takes(co, g)) return false;
     const int64_t lim = (int64_t)1 << 30;  // element offsets are 32-bit byte offsets
     auto fits = [&](const View &v, int c) { return (int64_t)g.n * v.sn + (int64_t)c * v.sc + (int64_t)g.h * g.w < lim; };
     if (!fits(in, ci) || !fits(out, co) || (r && !fits(*r, co)) || (int64_t)ci * co * ks * ks >= lim) return false;

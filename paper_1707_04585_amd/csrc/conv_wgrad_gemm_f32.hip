@@ -52,17 +52,17 @@ __device__ __forceinline__ int div_u(int e, int d, uint32_t m) {
     return e - q * d >= d ? q + 1 : q;
 }
 
-constexpr int lds_floats(int ks, int rows_a, int rows_b, int seg, int kw, int tiles) {
+constexpr int lds_floats(int ks, int rows_a, int rows_b, int seg, int tiles) {
     // odd pitches: the 32 rows an operand read touches fall into different banks
     const int stage = rows_a * (kChunk + 1) + rows_b * (seg * 64 + 1) + kChunk;
     const int sum = (ks == 3 ? 3 : tiles) * 1024 * kWaves;  // shares of three taps / of the tiles, added at the end
-    return kw > 1 && sum > stage ? sum : stage;
+    return sum > stage ? sum : stage;
 }
 
 // MW x CW x KW wavefronts, each with MT x CT tiles of 32x32 (ko, c) for all taps.
 template <int KS, int MT, int CT, int MW, int CW, int KW, int SEG>
 __global__ __launch_bounds__(kThreads, 2) void conv_wgrad_gemm_f32_k(const WgemmArgs p) {
-    static_assert(MW * CW * KW == kWaves, "four wavefronts");
+    static_assert(MW * CW * KW == kWaves && KW > 1, "four wavefronts, the pixels shared");
     constexpr int KS2 = KS * KS, NTILE = MT * CT;
     constexpr int RA = MT * MW * 32, RB = CT * CW * 32;  // channels of dh / of a in the workgroup's tile
     constexpr int PA = kChunk + 1, PB = SEG * 64 + 1;
@@ -178,17 +178,6 @@ __global__ __launch_bounds__(kThreads, 2) void conv_wgrad_gemm_f32_k(const Wgemm
     // ---- the workgroup's partial result in register order [tile][tap][register][lane]; the shares of the
     //      wavefronts that split the pixels are added in order
     float *out = p.part + (int64_t)slice * p.part_stride + (int64_t)grp * (MW * CW * NTILE * KS2 * 1024);
-    if (KW == 1) {
-#pragma unroll
-        for (int t = 0; t < NTILE; ++t) {
-            const int tl = (mw * MT + t / CT) * (CW * CT) + cw * CT + t % CT;
-#pragma unroll
-            for (int k = 0; k < KS2; ++k)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) out[((tl * KS2 + k) * 16 + i) * 64 + lane] = acc[t][k][i];
-        }
-        return;
-    }
     // rounds of RT results per wavefront: three taps of the one tile, or all tiles of the one tap
     constexpr int RT = KS == 3 ? 3 : NTILE;
     static_assert(KS == 1 || NTILE == 1, "one tile per wavefront for 3x3");
@@ -215,7 +204,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_wgrad_gemm_f32_k(const Wgemm
     }
 }
 
-// Tiles (in 32s) of a workgroup, by filter size: the shapes launch() instantiates.
+// Tiles (in 32s) of a workgroup for 1x1 filters: the shapes conv_wgrad_gemm_f32 launches.
 struct Tile {
     int m, c;
 };
@@ -269,13 +258,20 @@ WgemmPlan plan(int cin, int cout, int ks, const Geo &g, size_t scratch_floats) {
 
 template <int KS, int MT, int CT, int MW, int CW, int KW, int SEG>
 void run_one(Ctx &cx, const WgemmArgs &a) {
-    const size_t lds = (size_t)lds_floats(KS, MT * MW * 32, CT * CW * 32, SEG, KW, MT * CT) * 4;
+    const size_t lds = (size_t)lds_floats(KS, MT * MW * 32, CT * CW * 32, SEG, MT * CT) * 4;
     cx.run(conv_wgrad_gemm_f32_k<KS, MT, CT, MW, CW, KW, SEG>, dim3((unsigned)(a.slices * a.groups)), dim3(kThreads), lds, a);
 }
 
 uint32_t magic(int d) { return d == 1 ? 0u : (uint32_t)((1ull << 32) / (uint64_t)d); }
 
 }  // namespace
+
+// Which instance a layer runs on given the scratch it is planned with, for the tests: ks * 8 + pieces (3x3) or tile shape (1x1), or -1.
+extern "C" int rvn_conv_wgrad_gemm_f32_instance(int cin, int cout, int ks, int n, int h, int w) {
+    const Geo g{n, h, w};
+    const WgemmPlan p = plan(cin, cout, ks, g, wgrad_scratch_floats(cin, cout, ks, g));
+    return p.ok ? ks * 8 + (ks == 3 ? p.seg : p.shape) : -1;
+}
 
 bool conv_wgrad_gemm_f32(Ctx &cx, View x, const float *scale_shift, View dh, int cin, int cout, int ks, Geo g,
                          float *scratch, size_t scratch_floats, float *dw, bool accumulate, double bytes, double flops,
