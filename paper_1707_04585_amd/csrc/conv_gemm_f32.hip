@@ -25,11 +25,13 @@
 #include <algorithm>
 #include <cmath>
 
-#include "kernels.h"
+#include "flat_pixels.h"
 
 namespace rvn {
 
 namespace {
+
+using namespace flat;
 
 typedef float float16_t __attribute__((ext_vector_type(16)));
 
@@ -50,13 +52,6 @@ struct GemmArgs {
     int co_major;     // a die gets a range of output channels (else a range of pixels)
     uint32_t m_hw, m_w;
 };
-
-// e / d for 0 <= e < 2^31 with m = floor(2^32 / d) (m = 0: d = 1): the estimate is exact or one short.
-__device__ __forceinline__ int div_u(int e, int d, uint32_t m) {
-    if (m == 0) return e;
-    int q = (int)__umulhi((uint32_t)e, m);
-    return e - q * d >= d ? q + 1 : q;
-}
 
 // LDS of one buffer: the filter chunk [tap][channel][ko] with an odd pitch, then the staged planes.
 constexpr int buffer_floats(int ks, int bm, int kc, int pb) { return kc * ks * ks * (bm + 1) + kc * pb; }
@@ -361,8 +356,6 @@ bool launch_shape(Ctx &cx, const GemmArgs &a, int shape, Plane pl, dim3 grid) {
     return false;
 }
 
-uint32_t magic(int d) { return d == 1 ? 0u : (uint32_t)((1ull << 32) / (uint64_t)d); }
-
 // Fewer than 17 channels would leave half of a 32-row tile idle, and up to 32 channels in rows of whole
 // 4-pixel groups the row-band kernel also leaves the statistics of its output and shares a launch with
 // the filter gradient; above, and for every other row length, this kernel took a quarter to a half of its time.
@@ -382,9 +375,7 @@ extern "C" int rvn_conv_gemm_f32_instance(int ci, int co, int ks, int n, int h, 
 bool conv_gemm_f32(Ctx &cx, View in, const float *scale_shift, const float *w, bool transposed, int ci, int co, int ks,
                    Geo g, Epilogue ep, const View *r, View out) {
     if (!takes(co, g)) return false;
-    const int64_t lim = (int64_t)1 << 30;  // element offsets are 32-bit byte offsets
-    auto fits = [&](const View &v, int c) { return (int64_t)g.n * v.sn + (int64_t)c * v.sc + (int64_t)g.h * g.w < lim; };
-    if (!fits(in, ci) || !fits(out, co) || (r && !fits(*r, co)) || (int64_t)ci * co * ks * ks >= lim) return false;
+    if (!fits(in, ci, g) || !fits(out, co, g) || (r && !fits(*r, co, g)) || (int64_t)ci * co * ks * ks >= kMaxElems) return false;
     const int shape = choose_shape(g, ci, co, ks);
     if (shape < 0) return false;  // rows too wide for the staged planes
     const Shape &s = kShapes[shape];

@@ -108,6 +108,22 @@ Tiling choose_tiling(const Geo &g, int ks, int kc, int mt) {
     return best;
 }
 
+// Channel tiles per workgroup and channels per chunk.
+int tiles_of(int co) { return co <= 16 ? 1 : co <= 32 ? 2 : 4; }
+int chunk_of(int ks, int mt) { return ks == 3 && mt == 4 ? 8 : 16; }
+
+// Whether choose_tiling finds anything: the smallest pixel block it tries (one row of tiles of one image) fits.
+bool tiling_exists(const Geo &g, int ks, int kc, int mt) {
+    const int w16 = (g.w + 15) / 16 * 16, w8 = (g.w + 7) / 8 * 8;
+    Tiling t{};
+    t.tcols = w16 <= w8 ? 16 : 8;
+    t.trows = t.TH = 16 / t.tcols;
+    t.ctl = (g.w + t.tcols - 1) / t.tcols;
+    t.IMGS = 1;
+    set_geometry(t, ks, kc, mt);
+    return t.ctl <= kWaves * 7 && t.lds_bytes <= 64 * 1024;
+}
+
 template <int KS, int KC>
 void launch_conv(Ctx &cx, ConvArgs &a, const Tiling &tl, int mt, dim3 grid) {
 #define RVN_CASE(MT_, NT_)                                                                    \
@@ -122,12 +138,15 @@ void launch_conv(Ctx &cx, ConvArgs &a, const Tiling &tl, int mt, dim3 grid) {
 
 void conv_mfma(Ctx &cx, View in, const float *scale_shift, const float *w, bool transposed, int ci,
                int co, int ks, Geo g, bool bf16, Epilogue ep, const View *r, View out) {
+    // (rows too wide for a row-band tiling are refused whichever kernel would take them)
+    if (!bf16 && tiling_exists(g, ks, chunk_of(ks, tiles_of(co)), tiles_of(co)) &&
+        conv_gemm_f32(cx, in, scale_shift, w, transposed, ci, co, ks, g, ep, r, out))
+        return;
     ConvLaunch L;
     if (!conv_mfma_plan(in, scale_shift, w, transposed, ci, co, ks, g, bf16, ep, r, out, L)) {
         cx.fail(hipErrorInvalidConfiguration);  // no tiling fits (image rows too wide for LDS)
         return;
     }
-    if (!bf16 && conv_gemm_f32(cx, in, scale_shift, w, transposed, ci, co, ks, g, ep, r, out)) return;
     Tiling tl{};
     tl.NT = L.nt;
     tl.lds_bytes = L.lds_bytes;
@@ -157,8 +176,7 @@ void conv_mfma(Ctx &cx, View in, const float *scale_shift, const float *w, bool 
 
 bool conv_mfma_plan(View in, const float *scale_shift, const float *w, bool transposed, int ci, int co, int ks,
                     Geo g, bool bf16, Epilogue ep, const View *r, View out, ConvLaunch &L) {
-    const int mt = co <= 16 ? 1 : co <= 32 ? 2 : 4;
-    const int kc = ks == 3 ? (mt == 4 ? 8 : 16) : 16;
+    const int mt = tiles_of(co), kc = chunk_of(ks, mt);
     const Tiling tl = choose_tiling(g, ks, kc, mt);
     if (tl.NT == 0) return false;
     if ((int64_t)ci * co * ks * ks >= ((int64_t)1 << 30)) return false;  // filter elements are indexed in 32 bits

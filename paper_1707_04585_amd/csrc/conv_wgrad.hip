@@ -59,7 +59,8 @@ int bank_pad(int plane) {  // smallest value >= plane that is 4 modulo 64
     return plane + ((4 - plane % 64) + 64) % 64;
 }
 
-WgradPlan plan_wgrad(int cin, int cout, int ks, const Geo &g) {
+// probe: only whether there is a plan.
+WgradPlan plan_wgrad(int cin, int cout, int ks, const Geo &g, bool probe = false) {
     WgradPlan w{};
     w.MT = cout <= 16 ? 1 : 2;
     w.CT = cin <= 16 ? 1 : 2;
@@ -85,6 +86,8 @@ WgradPlan plan_wgrad(int cin, int cout, int ks, const Geo &g) {
         w.lds_bytes = bytes > red_bytes ? bytes : red_bytes;
         return true;
     };
+    w.ok = fits(1, 1);  // (nothing larger fits if this does not)
+    if (!w.ok || probe) return w;
     w.ok = false;
     for (int imgs = g.n < 8 ? g.n : 8; imgs >= 1 && !w.ok; --imgs) w.ok = fits(g.h, imgs);
     for (int th = g.h - 1; th >= 1 && !w.ok; --th) w.ok = fits(th, 1);
@@ -124,7 +127,7 @@ void conv_wgrad(Ctx &cx, View x, const float *scale_shift, rvn_dtype dt, View dh
                         P * cin * 4.0 + P * cout * 4.0, flops, defer))
         return;
     // (rows too wide for the row-band plan are refused whichever kernel would take them)
-    if (dt == RVN_F32 && plan_wgrad(cin, cout, ks, g).ok &&
+    if (dt == RVN_F32 && plan_wgrad(cin, cout, ks, g, true).ok &&
         conv_wgrad_gemm_f32(cx, x, scale_shift, dh, cin, cout, ks, g, scratch, scratch_floats, dw, accumulate,
                             P * cin * 4.0 + P * cout * 4.0, flops, defer))
         return;

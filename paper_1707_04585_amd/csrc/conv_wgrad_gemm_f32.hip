@@ -20,11 +20,13 @@
 // before): 1x1 95 -> 32 us, 3x3 111 -> 61 us; 28 -> 28 3x3 at 19x21, 51 images: 21.7 -> 15.5 us.
 #include <algorithm>
 
-#include "kernels.h"
+#include "flat_pixels.h"
 
 namespace rvn {
 
 namespace {
+
+using namespace flat;
 
 typedef float float16_t __attribute__((ext_vector_type(16)));
 
@@ -44,13 +46,6 @@ struct WgemmArgs {
     int part_stride;
     uint32_t m_hw, m_w;
 };
-
-// e / d for 0 <= e < 2^31 with m = floor(2^32 / d) (m = 0: d = 1): the estimate is exact or one short.
-__device__ __forceinline__ int div_u(int e, int d, uint32_t m) {
-    if (m == 0) return e;
-    int q = (int)__umulhi((uint32_t)e, m);
-    return e - q * d >= d ? q + 1 : q;
-}
 
 constexpr int lds_floats(int ks, int rows_a, int rows_b, int seg, int tiles) {
     // odd pitches: the 32 rows an operand read touches fall into different banks
@@ -262,8 +257,6 @@ void run_one(Ctx &cx, const WgemmArgs &a) {
     cx.run(conv_wgrad_gemm_f32_k<KS, MT, CT, MW, CW, KW, SEG>, dim3((unsigned)(a.slices * a.groups)), dim3(kThreads), lds, a);
 }
 
-uint32_t magic(int d) { return d == 1 ? 0u : (uint32_t)((1ull << 32) / (uint64_t)d); }
-
 }  // namespace
 
 // Which instance a layer runs on given the scratch it is planned with, for the tests: ks * 8 + pieces (3x3) or tile shape (1x1), or -1.
@@ -276,9 +269,7 @@ extern "C" int rvn_conv_wgrad_gemm_f32_instance(int cin, int cout, int ks, int n
 bool conv_wgrad_gemm_f32(Ctx &cx, View x, const float *scale_shift, View dh, int cin, int cout, int ks, Geo g,
                          float *scratch, size_t scratch_floats, float *dw, bool accumulate, double bytes, double flops,
                          WgradReduce *defer) {
-    const int64_t lim = (int64_t)1 << 30;  // element offsets are 32-bit byte offsets
-    auto fits = [&](const View &v, int c) { return (int64_t)g.n * v.sn + (int64_t)c * v.sc + (int64_t)g.h * g.w < lim; };
-    if (!fits(x, cin) || !fits(dh, cout)) return false;
+    if (!fits(x, cin, g) || !fits(dh, cout, g)) return false;
     const WgemmPlan w = plan(cin, cout, ks, g, scratch_floats);
     if (!w.ok) return false;
     WgradReduce red{};
