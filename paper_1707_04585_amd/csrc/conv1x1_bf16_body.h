@@ -216,28 +216,31 @@ __device__ __forceinline__ void conv1x1_bf16_body(const C1Args &p, int bx, int g
             return;
         } else {
         float v[8][4];
-        // (scalar loads of the scale and shift: several channels in one where no channel is clamped)
-        auto activate = [&](auto padded) {
+        auto activate = [&](int k, int c, int c8) {  // channel numbers of the two halves: wavefront-uniform, scalar loads
+            float x0 = b.v[k][0], x1 = b.v[k][1], x2 = b.v[k][2], x3 = b.v[k][3];
+            if (bn) {
+                const float s_lo = p.scale_shift[c], s_hi = p.scale_shift[c8];
+                const float h_lo = p.scale_shift[CI + c], h_hi = p.scale_shift[CI + c8];
+                const float sc = kg ? s_hi : s_lo, sh = kg ? h_hi : h_lo;
+                x0 = fmaxf(fmaf(x0, sc, sh), 0.f);
+                x1 = fmaxf(fmaf(x1, sc, sh), 0.f);
+                x2 = fmaxf(fmaf(x2, sc, sh), 0.f);
+                x3 = fmaxf(fmaf(x3, sc, sh), 0.f);
+            }
+            v[k][0] = x0; v[k][1] = x1; v[k][2] = x2; v[k][3] = x3;
+        };
+        if (RAGGED && ks * 16 + 16 > CI) {
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                float x0 = b.v[k][0], x1 = b.v[k][1], x2 = b.v[k][2], x3 = b.v[k][3];
-                if (bn) {
-                    const int c = padded ? min(ks * 16 + k, CI - 1) : ks * 16 + k;  // wavefront-uniform
-                    const int c8 = padded ? min(ks * 16 + k + 8, CI - 1) : c + 8;
-                    const float s_lo = p.scale_shift[c], s_hi = p.scale_shift[c8];
-                    const float h_lo = p.scale_shift[CI + c], h_hi = p.scale_shift[CI + c8];
-                    const float sc = kg ? s_hi : s_lo, sh = kg ? h_hi : h_lo;
-                    x0 = fmaxf(fmaf(x0, sc, sh), 0.f);
-                    x1 = fmaxf(fmaf(x1, sc, sh), 0.f);
-                    x2 = fmaxf(fmaf(x2, sc, sh), 0.f);
-                    x3 = fmaxf(fmaf(x3, sc, sh), 0.f);
-                }
-                const bool in = !padded || ks * 16 + kg * 8 + k < CI;
-                v[k][0] = in ? x0 : 0.f; v[k][1] = in ? x1 : 0.f; v[k][2] = in ? x2 : 0.f; v[k][3] = in ? x3 : 0.f;
+                activate(k, min(ks * 16 + k, CI - 1), min(ks * 16 + k + 8, CI - 1));
+                const bool in = ks * 16 + kg * 8 + k < CI;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[k][j] = in ? v[k][j] : 0.f;
             }
-        };
-        if (RAGGED && ks * 16 + 16 > CI) activate(std::true_type{});
-        else activate(std::false_type{});
+        } else {  // (no clamping: several channels' scales in one scalar load)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) activate(k, ks * 16 + k, ks * 16 + k + 8);
+        }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const uint4_t bq = {pack2(v[0][j], v[1][j]), pack2(v[2][j], v[3][j]), pack2(v[4][j], v[5][j]),
