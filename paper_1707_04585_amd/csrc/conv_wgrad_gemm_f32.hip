@@ -236,6 +236,7 @@ WgemmPlan plan(int cin, int cout, int ks, const Geo &g, size_t scratch_floats) {
     w.tiles_ko = (cout + w.m * 32 - 1) / (w.m * 32);
     w.tiles_c = (cin + w.c * 32 - 1) / (w.c * 32);
     w.groups = w.tiles_ko * w.tiles_c;
+    if ((int64_t)w.groups * w.m * w.c * ks * ks * 1024 > 0x7fffffff) return w;  // a partial result is indexed in 32 bits
     w.part_stride = w.groups * w.m * w.c * ks * ks * 1024;
     w.chunks = (int)((g.pixels() + kChunk - 1) / kChunk);
     int s = std::max(1, 512 / w.groups);  // two workgroups per compute unit

@@ -174,6 +174,15 @@ def test_ragged_bf16_layers_take_their_statistics_from_a_pass_over_the_tensor(ki
     assert abs(per_pixel[0] / per_pixel[1] - 1) < 0.01, per_pixel
 
 
+def test_cost_query_takes_the_largest_descriptors():
+    """65536 channels, the most a descriptor allows: counted as any other, although no filter gradient of that size
+    (2^32 elements per partial result) fits the 32-bit indices of the flat-pixel kernel."""
+    for c_half, width in ((65536, 65536), (46341, 46341), (65536, 64)):
+        fwd, bwd = rv.revnet_stack_cost(rv.BlockDesc("bottleneck", c_half, width), 1, 2, 7, 7)
+        assert (fwd["conv_fwd_calls"], bwd["conv_wgrad_calls"]) == (6, 6)
+        assert bwd["kernel_launches"] == 31
+
+
 def test_down_block_and_body_argument_validation():
     """The subsampling block and the body check shapes, channel chains, even
     sizes, overlaps and the workspace before anything is enqueued."""
