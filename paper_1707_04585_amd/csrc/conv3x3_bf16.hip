@@ -135,8 +135,9 @@ C3Plan plan_c3(int ci, int co, const Geo &g, int stride = 1) {
     const int64_t wgs = (int64_t)((g.n + pl.IMGS - 1) / pl.IMGS) * pl.bands * ((co + ch - 1) / ch);
     pl.S = 1;
     // Ragged octets: taken where the unsplit launch fills the chip (66 -> 66 channels in two bottleneck
-    // blocks, 64 images of 56x56: 4.76 ms per training step with conv_bf16_k, 4.34 with this kernel); below
-    // that, conv_bf16_k has smaller pixel blocks and needs no partial tiles.
+    // blocks, 64 images of 56x56: 4.70 ms per training step with conv_bf16_k, 4.32 with this kernel; 33 -> 33 in
+    // two basic blocks, 36 of 32x32: 786 and 675 us); below that, conv_bf16_k has smaller pixel blocks and needs
+    // no partial tiles.
     if (ragged && wgs <= 128) {
         pl.ok = false;
         return pl;

@@ -5,23 +5,32 @@
 // pixels of the batch: a tile is BN consecutive pixels, whatever the image sides are, so nothing is
 // padded to rows, images or 4-pixel groups, and one form serves every width and alignment.  A tap of a
 // 3x3 filter is the constant distance (r - 1) * W + (s - 1) along p, so a workgroup stages, per input
-// channel, the BN + 2W + 2 consecutive values its tile can touch (1.9 loads per pixel and channel at 56
-// columns, 1.2 at 14, for BN = 128); the taps that leave the image read a zero kept at the end of each
-// staged plane, by one address select per tap and tile.
+// channel, the BN + 2W + 2 consecutive values its tile can touch, in whole pieces of 64 (2.0 loads per pixel
+// and channel for BN = 128, at 56 columns and at 14 alike: what lies past them is loaded and not used); the taps
+// that leave the image read a zero kept at the end of each staged plane, by one address select per tap and tile.
 //
-// What bounds it.  v_mfma_f32_32x32x2_f32 takes 64 cycles for two operand words per lane, so LDS and
-// load issue have slack and the matrix pipe is the bound as long as the loads are out of the way: the next
-// chunk's activations and filters are requested into registers before the matrix instructions of the
-// present one and written to the other LDS buffer after them (one barrier per chunk).  A lane's pixel
-// offset is fixed for the whole kernel and the channel is wavefront-uniform, so a staged element costs
-// one load with a scalar base, one fma, one max and one LDS write.  Where the output is small, a
-// workgroup's wavefronts share one tile and split the channels (KW), summed through LDS in a fixed order,
-// instead of leaving compute units idle.
+// Pipeline.  v_mfma_f32_32x32x2_f32 takes 64 cycles for two operand words per lane.  The next chunk's
+// activations and filters are requested into registers before the matrix instructions of the present one and
+// written to the other LDS buffer after them (one barrier per chunk).  A lane's pixel offset is fixed for the
+// whole kernel and the channel is wavefront-uniform, so a staged element costs one load with a scalar base, one
+// fma, one max and one LDS write.  Where the output is small, a workgroup's wavefronts share one tile and split
+// the channels (KW), summed through LDS in a fixed order, instead of leaving compute units idle.
+//
+// What bounds it, by leaving parts out (four-stage network, 16 images; 3x3, 3.7 GFLOP a layer, 64 x 128 tiles):
+//                                    128 -> 128 at 28x28,    64 -> 64 at 56x56,
+//                                    200 workgroups          392 workgroups
+//   whole kernel                     57 us                   51 us
+//   without the loads                55                      51
+//   and without the LDS writes       49                      48
+//   and without the tap selects      46                      45
+//   matrix instructions alone        31                      31
+// so most of it is the matrix loop itself (operand reads and their waits, barriers, prologue, epilogue), not the
+// memory round trip.  The small tiles do wait for memory: without the loads the 512 -> 512 layer at 7x7 takes 67 us
+// of 81, 1x1 layers with 64-channel chunks 20 to 23 of 28 to 50.
 //
 // Measured (mean over the layers of the four-stage 50176-pixel-to-784-pixel bottleneck network, 16 images;
-// the row-band kernel before): 1x1 132 -> 28 us, 3x3 314 -> 73 us, of which the 512 -> 512 layer at 7x7
-// takes 79 us (113 with 8-channel chunks, a chain of 64 memory round trips); 28 -> 28 3x3 at 19x21,
-// 51 images: 25.7 -> 14.7 us.
+// the row-band kernel before): 1x1 132 -> 28 us, 3x3 314 -> 73 us (the 512 -> 512 layer at 7x7 takes 113 us
+// with 8-channel chunks, 81 with 16); 28 -> 28 3x3 at 19x21, 51 images: 25.7 -> 14.7 us.
 #include <algorithm>
 #include <cmath>
 
@@ -305,7 +314,8 @@ Plane plane_of(const Shape &s, int w) {
 
 // The tile shape with the smallest estimated time in cycles.  A compute unit holds two workgroups at a
 // time; they take the larger of their matrix and staging work (256 flop and 16 bytes per cycle) and of one
-// workgroup's chain of chunks, each a memory round trip (about 3500 cycles under load) or its matrix work.
+// workgroup's chain of chunks, each a memory round trip (taken as 3500 cycles) or its matrix work.  It ranks the
+// shapes and does not predict times: 35 and 42 us for the two layers above that take 57 and 51.
 int choose_shape(const Geo &g, int ci, int co, int ks) {
     int best = -1;
     double best_cost = 0.0;
@@ -357,8 +367,11 @@ bool launch_shape(Ctx &cx, const GemmArgs &a, int shape, Plane pl, dim3 grid) {
 }
 
 // Fewer than 17 channels would leave half of a 32-row tile idle, and up to 32 channels in rows of whole
-// 4-pixel groups the row-band kernel also leaves the statistics of its output and shares a launch with
-// the filter gradient; above, and for every other row length, this kernel took a quarter to a half of its time.
+// 4-pixel groups the row-band kernel of a 3x3 layer also leaves the statistics of its output and shares a launch
+// with the filter gradient; above, and for every other row length, this kernel took a quarter to a half of its
+// time.  1x1 layers of up to 32 channels have neither advantage and stay there only because the line was drawn for
+// 3x3: with them and their filter gradients here, two bottleneck blocks of 64 channels reduced to 32 take 884 us
+// instead of 1196 (8 images of 28x28), of 128 to 32 2136 instead of 2302 (32 of 56x56), and no shape tried took longer.
 bool takes(int co, const Geo &g) { return co > 32 || (co > 16 && (g.w & 3) != 0); }
 
 }  // namespace

@@ -7,14 +7,19 @@
 // 64 + 2W + 2 (a) consecutive values per channel.  A tap that leaves the image is a zero of `a`: a nine-bit
 // mask per pixel, made once per chunk, is spread to an all-ones / all-zeros word and ANDed to the operand.
 //
-// What bounds it.  One v_mfma_f32_32x32x2_f32 takes 64 cycles for two operand words, so the matrix pipe
-// is the bound once loads are hidden: the next chunk is requested into registers before the matrix
-// instructions of the present one.  A 3x3 wavefront holds one 32x32 tile for all nine taps (144
+// Pipeline.  One v_mfma_f32_32x32x2_f32 takes 64 cycles for two operand words; the next chunk is requested
+// into registers before the matrix instructions of the present one.  A 3x3 wavefront holds one 32x32 tile for all nine taps (144
 // accumulators) and the workgroup's four wavefronts share the tile and split the pixels, which costs no
 // partial results in memory; a 1x1 wavefront holds 2x2 tiles, because with one tap the words staged per
 // flop would otherwise exceed what the last-level cache delivers.  Slices of the pixels go to further
 // workgroups until two are resident per compute unit, or as many as the caller's scratch has room for;
 // their partial results are summed by wgrad_reduce_body in a fixed order (no floating-point atomics).
+//
+// What bounds it (four-stage network, 16 images, parts left out as a measurement): not the loads.  3x3, 448
+// workgroups: 51 us, 50 without the loads, 47 without the LDS writes as well, for 24 of matrix work: the matrix loop (an
+// operand read, a mask and a wait per tap) and the sums at the end.  1x1, 272 workgroups: 31, 31 and 27 us for 5.3 of
+// matrix work: one LDS buffer and two barriers a chunk, 32 operands that each wait for LDS, and the partial results;
+// its 64-bit channel bases do not fit the scalar registers either (97 to 279 spills).
 //
 // Measured (mean over the layers of the four-stage bottleneck network, 16 images; the row-band kernel
 // before): 1x1 95 -> 32 us, 3x3 111 -> 61 us; 28 -> 28 3x3 at 19x21, 51 images: 21.7 -> 15.5 us.
@@ -215,7 +220,7 @@ WgemmPlan plan(int cin, int cout, int ks, const Geo &g, size_t scratch_floats) {
     const int seg = ks == 3 ? (kChunk + 2 * g.w + 2 + 63) / 64 : 1;
     if (seg > 4) return w;  // rows too wide for the staged runs
     // 16 channels on either side leave half of a 32x32 tile idle, and up to 32 in rows of whole 4-pixel
-    // groups the layer's two gradients share a launch of the row-band kernels.
+    // groups a 3x3 layer's two gradients share a launch of the row-band kernels (1x1 layers: see conv_gemm_f32.hip).
     if (std::min(cin, cout) <= 16 || (std::max(cin, cout) <= 32 && (g.w & 3) == 0)) return w;
     w.seg = seg;
     w.m = w.c = 1;
