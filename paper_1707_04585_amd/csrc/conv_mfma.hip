@@ -140,7 +140,8 @@ void conv_mfma(Ctx &cx, View in, const float *scale_shift, const float *w, bool 
                int co, int ks, Geo g, bool bf16, Epilogue ep, const View *r, View out) {
     // (rows too wide for a row-band tiling are refused whichever kernel would take them)
     if (!bf16 && tiling_exists(g, ks, chunk_of(ks, tiles_of(co)), tiles_of(co)) &&
-        conv_gemm_f32(cx, in, scale_shift, w, transposed, ci, co, ks, g, ep, r, out))
+        ((ks == 3 && conv3x3_f32(cx, in, scale_shift, w, transposed, ci, co, g, ep, r, out)) ||
+         conv_gemm_f32(cx, in, scale_shift, w, transposed, ci, co, ks, g, ep, r, out)))
         return;
     ConvLaunch L;
     if (!conv_mfma_plan(in, scale_shift, w, transposed, ci, co, ks, g, bf16, ep, r, out, L)) {

@@ -236,6 +236,11 @@ void conv_fwd(Ctx &cx, View x, const float *scale_shift, rvn_dtype dt, const flo
 bool conv_gemm_f32(Ctx &cx, View in, const float *scale_shift, const float *w, bool transposed, int ci, int co, int ks,
                    Geo g, Epilogue ep, const View *r, View out);
 
+// The 3x3 convolution of narrow layers with fp32 operands (conv3x3_f32.hip); returns false (nothing launched)
+// for the shapes it does not take.
+bool conv3x3_f32(Ctx &cx, View in, const float *scale_shift, const float *w, bool transposed, int ci, int co, Geo g,
+                 Epilogue ep, const View *r, View out);
+
 // The same convolution on bf16 matrix instructions (operands rounded to bf16,
 // fp32 accumulation); `transposed`: w is [ci][co][ks][ks] and is read transposed
 // and flipped (data gradient).  Returns false if no tiling fits (nothing is

@@ -1,0 +1,40 @@
+"""fp32 3x3 layers of up to 32 channels, at the sizes where the pixel blocks, staging passes and channel tiles of
+their kernels end, against the oracle in float64 (the check and its bars are those of the flat-pixel kernels)."""
+import pytest
+
+import test_gpu_conv_gemm as G
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # one pixel an image (not with one channel: the BN layer behind it removes its scale, and with it the gradient)
+    dict(n=40, c=10, h=1, w=1),
+    dict(n=3, c=6, h=5, w=3),          # a quad longer than the row
+    dict(n=37, c=30, h=2, w=2),        # many images per block, the last block not full
+    dict(n=4, c=16, h=8, w=8),         # one block, whole
+    dict(n=5, c=32, h=8, w=8),         # a last block of one image; 16 channels
+    dict(n=2, c=32, h=9, w=32),        # a last band of one row
+    dict(n=3, c=26, h=7, w=65),        # 17 quads a row, 8 staging passes, ragged
+    dict(n=2, c=18, h=6, w=64),        # 16 quads a row, 8 staging passes
+    dict(n=2, c=32, h=4, w=160),       # widest rows with a backward plan
+    dict(n=2, c=34, h=3, w=166),       # nearly the widest rows taken; forward only
+    dict(n=1, c=34, h=2, w=172),       # too wide: row-band kernel; forward only
+    dict(n=6, c=34, h=11, w=13),       # a second channel tile of one channel, a second chunk of one
+    dict(n=3, c=64, h=16, w=16),       # two full channel tiles, whole blocks
+    dict(n=130, c=34, h=32, w=15),     # 256 blocks and more: both channel tiles in one workgroup; ragged
+    dict(n=64, c=40, h=16, w=64),      # the same with 8 staging passes, rows of whole quads
+    dict(n=86, c=36, h=9, w=66),       # the same, ragged
+    dict(n=128, c=64, h=16, w=32),     # the same, whole blocks
+]
+# flat-pixel instances that the cases of their own test reach through layers of up to 32 channels
+WIDER = [
+    dict(n=22, c=130, h=12, w=32), dict(n=6, c=130, h=19, w=72), dict(n=10, c=66, h=10, w=42),
+    dict(n=1, c=66, h=1, w=35), dict(n=1, c=66, h=1, w=48),
+]
+
+
+@pytest.mark.parametrize("case", CASES + WIDER, ids=lambda k: "n%d c%d %dx%d" % (k["n"], k["c"], k["h"], k["w"]))
+def test_block_against_oracle(case, monkeypatch):
+    if case["c"] <= 32:  # (the filter gradient's limit on the row length is twice that of wider layers)
+        monkeypatch.setattr(G, "WIDEST_BACKWARD", 160)
+    G.test_block_against_oracle(dict(kind="basic", **case))
