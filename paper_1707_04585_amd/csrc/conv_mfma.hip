@@ -34,10 +34,10 @@ namespace {
 
 constexpr int kThreads = kConvThreads;
 
-template <int KS, int MT, int NT, int KC, bool EMIT = false>
+template <int KS, int MT, int NT, int KC>
 __global__ __launch_bounds__(kThreads) void conv_mfma_f32_k(const ConvArgs p) {
     extern __shared__ __align__(16) float smem[];
-    conv_mfma_f32_body<KS, MT, NT, KC, EMIT>(p, blockIdx.x, blockIdx.y, smem);
+    conv_mfma_f32_body<KS, MT, NT, KC>(p, blockIdx.x, blockIdx.y, smem);
 }
 
 uint32_t fdiv_magic(int d) { return d == 1 ? 0u : (uint32_t)((1ull << 32) / (uint64_t)d + 1ull); }
@@ -152,19 +152,6 @@ void conv_mfma(Ctx &cx, View in, const float *scale_shift, const float *w, bool 
     tl.NT = L.nt;
     tl.lds_bytes = L.lds_bytes;
     ConvArgs a = L.a;
-    // Statistics of the output for the BN layer that reads it next (fp32 operands, 3x3, up to 32 output
-    // channels, 4 tiles per wavefront): every tile slot of every workgroup must be a whole, valid tile.
-    const int tiles = (int)L.grid.x * kWaves;
-    const bool whole = a.whole != 0;
-    if (cx.want_emit && cx.emit_buf && !bf16 && !transposed && ks == 3 && L.kc == 16 && L.nt == 4 && L.mt <= 2 &&
-        whole && (size_t)co * tiles * 2 <= cx.emit_floats) {
-        a.emit = cx.emit_buf;
-        a.emit_tiles = tiles;
-        cx.emitted = EmittedStats{out.p, out.sn, out.sc, co, g.n, g.h, g.w, tiles, 16 * L.nt};
-        if (L.mt == 1) cx.run(conv_mfma_f32_k<3, 1, 4, 16, true>, L.grid, dim3(kThreads), tl.lds_bytes, a);
-        else cx.run(conv_mfma_f32_k<3, 2, 4, 16, true>, L.grid, dim3(kThreads), tl.lds_bytes, a);
-        return;
-    }
     if (ks == 3) {
         if (L.kc == 8) launch_conv<3, 8>(cx, a, tl, L.mt, L.grid);
         else launch_conv<3, 16>(cx, a, tl, L.mt, L.grid);

@@ -110,6 +110,8 @@ WgradPlan plan_wgrad(int cin, int cout, int ks, const Geo &g, bool probe = false
 
 }  // namespace
 
+bool wgrad_rows_fit(int cin, int cout, int ks, const Geo &g) { return plan_wgrad(cin, cout, ks, g, true).ok; }
+
 size_t wgrad_scratch_floats(int cin, int cout, int ks, const Geo &g) {
     const WgradPlan w = plan_wgrad(cin, cout, ks, g);
     return std::max(w.ok ? (size_t)w.S * w.part_stride : 0, wgrad_bf16_scratch_floats(cin, cout, ks, g));
@@ -126,8 +128,7 @@ void conv_wgrad(Ctx &cx, View x, const float *scale_shift, rvn_dtype dt, View dh
         conv_wgrad_bf16(cx, x, scale_shift, dh, cin, cout, ks, g, scratch, dw, accumulate,
                         P * cin * 4.0 + P * cout * 4.0, flops, defer))
         return;
-    // (rows too wide for the row-band plan are refused whichever kernel would take them)
-    if (dt == RVN_F32 && plan_wgrad(cin, cout, ks, g, true).ok &&
+    if (dt == RVN_F32 && wgrad_rows_fit(cin, cout, ks, g) &&
         conv_wgrad_gemm_f32(cx, x, scale_shift, dh, cin, cout, ks, g, scratch, scratch_floats, dw, accumulate,
                             P * cin * 4.0 + P * cout * 4.0, flops, defer))
         return;

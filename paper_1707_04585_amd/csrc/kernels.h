@@ -190,6 +190,9 @@ int reduce_splits(int c, const Geo &g);
 size_t bn_scratch_floats(int c, const Geo &g);
 // Scratch floats for the filter-gradient partial sums.
 size_t wgrad_scratch_floats(int cin, int cout, int ks, const Geo &g);
+// Whether the rows of a layer are short enough for the row-band filter gradient; longer ones are refused, whichever
+// kernel would take them.
+bool wgrad_rows_fit(int cin, int cout, int ks, const Geo &g);
 size_t wgrad_bf16_scratch_floats(int cin, int cout, int ks, const Geo &g);
 
 // ---- batch norm + ReLU (Section 2.2: a(x) = ReLU(BN(x))) -------------------
@@ -296,9 +299,9 @@ void wgrad_reduce(Ctx &cx, const WgradReduce &r);
 // results do not depend on it, bit for bit).
 bool separate_launches();
 
-// conv_dgrad and conv_wgrad of one fp32 3x3 layer in a single launch (both need
-// only dh); the ordered sum of the filter gradient is left in *defer.  Returns
-// false (nothing launched, nothing accounted) for the shapes it does not take.
+// conv_dgrad and conv_wgrad of one fp32 3x3 layer of up to 32 channels in a single launch (conv3x3_f32_bwd.hip; as two
+// launches, with the same bits, while separate_launches()); the ordered sum of the filter gradient is left in *defer.
+// Returns false (nothing launched, nothing accounted) for the shapes it does not take.
 bool conv_dgrad_wgrad_f32(Ctx &cx, View x, const float *scale_shift, View dh, const float *w, int cin, int cout,
                           int ks, Geo g, float *scratch, float *dw, bool accumulate, float *da, WgradReduce *defer);
 
