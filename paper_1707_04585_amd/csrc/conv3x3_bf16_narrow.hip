@@ -1,0 +1,190 @@
+// 3x3 convolution with bf16 operands of layers of up to 64 channels that are small enough to be bound by the chain of
+// one workgroup, for the units c_3(x) = Conv_3x3(ReLU(BN(x))) of Section 2.2.
+//
+// What bounds such a launch: set-up, one round trip to memory, staging, operand reads, stores; the matrix
+// instructions themselves are 0.1 to 0.4 us.  So the whole reduction is staged at once and multiplied without a second
+// barrier, and every phase is kept short:
+//  * all loads of a thread -- 8 channels of one 4-pixel group, scale and shift, filter, skip values -- are issued
+//    before the first of them is used; what lies outside is loaded from past the buffer's end, which gives zero;
+//  * the filter goes from memory to operand registers, without LDS; a filter that the driver has not converted is
+//    converted there (the 72 taps of an octet of input channels are consecutive);
+//  * pixels lie on M and channels on N of v_mfma_f32_32x32x16_bf16, so four consecutive results of a lane are
+//    consecutive pixels of one channel: 16-byte stores, and statistics that need few shuffles;
+//  * blocks shrink (256 to 64 pixels) until every compute unit has one, instead of a split of the channels with a second
+//    launch that sums it.
+// Sums and statistics keep the order of conv3x3_bf16 (Order in conv3x3_bf16_narrow_body.h), so a layer's results do not depend on which of the two
+// kernels its size goes to.
+// Measured, forward launch with statistics (register-tiled kernel before): 16 -> 16 channels, 8 images of 32x32 8.8 -> 4.7 us,
+// 128 images 13.0 -> 8.4; 32 -> 32, 128 of 16x16 12.5 -> 6.6; 56 -> 56, 128 of 8x8 10.8 + 4.2 (sum of the split) -> 6.6.
+// With v_mfma_f32_16x16x32_bf16 (two taps of 16 channels an instruction, blocks down to 64 pixels) the 16-channel launches took
+// 7.0 and 3.8 us, the others as long; sums in that order turned roundings of later layers.
+#include <algorithm>
+
+#include "conv3x3_bf16_narrow_body.h"
+#include "kernels.h"
+
+namespace rvn {
+
+namespace {
+
+using namespace c3n;
+
+template <int NT, int CH, int PASSES, bool GEN, bool EMIT, bool W32, int ORDER>
+__global__ __launch_bounds__(kThreads, 2) void conv3x3_bf16_narrow_k(const C3nArgs p) {
+    extern __shared__ __align__(16) char smem_c[];
+    conv3x3_bf16_narrow_body<NT, CH, PASSES, GEN, EMIT, W32, ORDER>(p, blockIdx.x, smem_c);
+}
+
+// Multiplier of fdiv_c3f: exact for e * d < 2^32 (e is a thread or block index here).
+uint32_t mul_of(int d) { return d == 1 ? 0u : (uint32_t)((1ull << 32) / (uint64_t)d + 1ull); }
+
+struct C3nPlan {
+    C3nShape s;
+    int passes;  // 0: no block fits
+    int64_t blocks;
+    size_t lds_bytes;
+};
+
+// The pixel block of a workgroup: whole rows of one image, or whole images, of at most `slots` quads.
+C3nPlan plan_c3n(const Geo &g, int slots, int ch) {
+    C3nPlan best{};
+    double best_score = -1.0;
+    const int wq = (g.w + 3) / 4, octs = ch / 8, pitch = 4 * wq + 1;
+    for (int imgs = 1; imgs <= slots && imgs <= g.n; ++imgs) {
+        for (int th = imgs > 1 ? g.h : 1; th <= g.h; ++th) {
+            const int quads = imgs * th * wq, bquads = imgs * (th + 2) * wq, items = bquads * octs;
+            const size_t lds = ((size_t)imgs * (th + 2) * pitch + 1) * record_bytes(ch);
+            if (quads > slots || items > 2 * kThreads || lds > 64 * 1024) break;
+            const int64_t bands = (g.h + th - 1) / th, blocks = bands * ((g.n + imgs - 1) / imgs);
+            const double score = (double)g.n * g.h * wq / ((double)blocks * slots) - (items > kThreads ? 0.02 : 0.0);
+            if (score <= best_score + 1e-9) continue;
+            best_score = score;
+            best.passes = items > kThreads ? 2 : 1;
+            best.blocks = blocks;
+            best.lds_bytes = std::max(lds, (size_t)2 * 64 * 64);  // (two wavefronts' results, for the statistics)
+            C3nShape &s = best.s;
+            s.N = g.n; s.H = g.h; s.W = g.w;
+            s.TH = th; s.IMGS = imgs; s.bands = (int)bands; s.wq = wq; s.quads = quads; s.lrows = th + 2; s.pitch = pitch;
+            s.bquads = bquads; s.items = items;
+        }
+    }
+    if (best.passes == 0 || best.blocks * best.s.bands >= ((int64_t)1 << 32)) return C3nPlan{};
+    C3nShape &s = best.s;
+    s.m_bands = mul_of(s.bands); s.m_bq = mul_of(s.bquads); s.m_rq = mul_of(s.lrows * s.wq);
+    s.m_wq = mul_of(s.wq); s.m_q = mul_of(s.TH * s.wq);
+    return best;
+}
+
+int class_of(int ci, int co) {
+    const int most = std::max(ci, co);
+    return most <= 16 ? 16 : most <= 32 ? 32 : most <= 64 ? 64 : 0;
+}
+
+// Where the line lies (forward pass of two basic blocks, us, kernels before / this one; beyond the line with 16x16 tiles):
+//  * 33 to 64 channels: a block reads the whole filter (73 KB from L2) for 128 pixels at most, and the register-tiled kernel
+//    for 256 as soon as it has enough blocks not to split the channels.  64 channels: 32 of 32x32 242 / 148, 8 of 56x56 221 /
+//    177; beyond, 10 of 56x56 177 / 215, 128 of 32x32 256 / 374.  A filter that is converted here costs twice the reads:
+//    44 channels, 13 of 27x23 133 / 102; 60, 64 of 13x13 141 / 126; beyond, 36, 8 of 40x40 163 / 174, 33, 64 of 16x16 163 / 166.
+//  * 17 to 32 channels in rows that are not whole quads: 28 channels, 51 of 19x21 122 / 100, 26, 128 of 20x20 (whole quads) 129 /
+//    111; beyond, 32, 128 of 31x31 165 / 170, 28, 64 of 55x55 231 / 237.  In rows of whole quads there is no such
+//    size: 32 channels, 128 of 56x56 404 / 369.
+//  * up to 16 channels: 0.59 to 0.96 over 16 shapes from four images of 2x2 to 64 of 112x112.
+bool takes(int cls, bool converted, const Geo &g) {
+    if (cls == 64) return g.pixels() <= (converted ? 32768 : 11264);
+    if (cls == 32) return g.w % 4 == 0 || g.pixels() <= 65536;
+    return cls == 16;
+}
+
+struct C3nLaunch {
+    C3nArgs a;
+    int cls, nt, passes, order;  // cls: 16, 32 or 64 channels
+    bool gen, whole;
+    dim3 grid;
+    size_t lds_bytes;
+};
+
+template <int NT, int CH, int PASSES, int ORDER>
+void launch_converted(Ctx &cx, const C3nLaunch &L) {
+    if (L.gen) cx.run(conv3x3_bf16_narrow_k<NT, CH, PASSES, true, false, false, ORDER>, L.grid, dim3(kThreads), L.lds_bytes, L.a);
+    else if (L.a.emit) cx.run(conv3x3_bf16_narrow_k<NT, CH, PASSES, false, true, false, ORDER>, L.grid, dim3(kThreads), L.lds_bytes, L.a);
+    else cx.run(conv3x3_bf16_narrow_k<NT, CH, PASSES, false, false, false, ORDER>, L.grid, dim3(kThreads), L.lds_bytes, L.a);
+}
+
+template <int NT, int CH, int PASSES>
+void launch_c3n(Ctx &cx, const C3nLaunch &L) {
+    if (!L.a.wq) {
+        cx.run(conv3x3_bf16_narrow_k<NT, CH, PASSES, true, false, true, CH == 16 ? kChunks : kTaps>, L.grid, dim3(kThreads), L.lds_bytes, L.a);
+        return;
+    }
+    if constexpr (CH == 32) {
+        if (L.order == kTaps) return launch_converted<NT, CH, PASSES, kTaps>(cx, L);
+    }
+    if constexpr (CH == 64) {
+        if (L.order == kHalves) return launch_converted<NT, CH, PASSES, kHalves>(cx, L);
+    }
+    launch_converted<NT, CH, PASSES, kChunks>(cx, L);
+}
+
+bool plan_launch(View in, const float *scale_shift, const float *w, const uint16_t *wq, int ci, int co, Geo g, Epilogue ep,
+                 const View *r, View out, C3nLaunch &L) {
+    L.cls = class_of(ci, co);
+    if (!takes(L.cls, wq != nullptr, g)) return false;
+    const int wp = 4 / chan_waves(L.cls);
+    C3nPlan pl{};
+    // The larger block if it still gives every compute unit one (where the filter is converted in the kernel, every
+    // second one).
+    for (int nt = 2; nt >= 1; --nt) {
+        const C3nPlan next = plan_c3n(g, 8 * nt * wp, L.cls);
+        if (next.passes == 0) continue;
+        pl = next;
+        L.nt = nt;
+        if (pl.blocks >= (wq ? 256 : 128)) break;
+    }
+    if (pl.passes == 0) return false;
+    // bytes from the base to the end of the last plane; every one must end below kNowhere
+    const int64_t in_b = 4 * ((g.n - 1) * in.sn + (ci - 1) * in.sc + g.hw()), out_b = 4 * ((g.n - 1) * out.sn + (co - 1) * out.sc + g.hw());
+    const int64_t r_b = r ? 4 * ((g.n - 1) * r->sn + (co - 1) * r->sc + g.hw()) : 0;
+    if (std::max(std::max(in_b, out_b), r_b) >= (int64_t)kNowhere) return false;
+    C3nArgs a{};
+    a.in = in.p; a.scale_shift = scale_shift; a.wq = wq; a.w = w; a.r = r ? r->p : nullptr; a.out = out.p;
+    a.isn = (uint32_t)in.sn; a.isc = (uint32_t)in.sc;
+    a.rsn = r ? (uint32_t)r->sn : 0; a.rsc = r ? (uint32_t)r->sc : 0;
+    a.osn = (uint32_t)out.sn; a.osc = (uint32_t)out.sc;
+    a.CI = ci; a.CO = co; a.CIP = (ci + 7) / 8 * 8; a.ep = (int)ep;
+    a.in_bytes = (uint32_t)in_b; a.out_bytes = (uint32_t)out_b; a.r_bytes = (uint32_t)r_b; a.w_bytes = (uint32_t)(wq ? co * 9 * a.CIP * 2 : co * ci * 36);
+    a.s = pl.s;
+    L.a = a;
+    L.gen = g.w % 4 != 0 || ci % 8 != 0 || !wq;
+    L.whole = g.w % 4 == 0 && pl.s.quads == 8 * L.nt * wp && g.n % pl.s.IMGS == 0 && g.h % pl.s.TH == 0;
+    L.passes = pl.passes;
+    // (the sums of conv3x3_bf16: chunks of 16 channels, or of 32 where that is all, in two partial results where it splits)
+    L.order = ci == 32 ? kTaps : conv3x3_bf16_scratch_floats(ci, co, g) > 0 ? kHalves : kChunks;
+    L.grid = dim3((unsigned)pl.blocks);
+    L.lds_bytes = pl.lds_bytes;
+    return true;
+}
+
+}  // namespace
+
+bool conv3x3_bf16_narrow(Ctx &cx, View in, const float *scale_shift, const float *w, const uint16_t *wq, int ci, int co, Geo g, Epilogue ep,
+                         const View *r, View out) {
+    C3nLaunch L;
+    if (!plan_launch(in, scale_shift, w, wq, ci, co, g, ep, r, out, L)) return false;
+    const int tiles = (int)((int64_t)g.pixels() / 64);
+    // (not for ragged channel counts, as in conv1x1_bf16)
+    if (cx.want_emit && cx.emit_buf && !L.gen && L.whole && (size_t)co * tiles * 2 <= cx.emit_floats) {
+        L.a.emit = cx.emit_buf;
+        L.a.emit_tiles = tiles;
+        cx.emitted = EmittedStats{out.p, out.sn, out.sc, co, g.n, g.h, g.w, tiles, 64};
+    }
+#define RVN_CASE(NT_, CH_)                                                \
+    if (L.cls == CH_ && L.nt == NT_) {                                    \
+        if (L.passes == 1) launch_c3n<NT_, CH_, 1>(cx, L);                \
+        else launch_c3n<NT_, CH_, 2>(cx, L);                              \
+    }
+    RVN_CASE(1, 16) RVN_CASE(2, 16) RVN_CASE(1, 32) RVN_CASE(2, 32) RVN_CASE(1, 64) RVN_CASE(2, 64)
+#undef RVN_CASE
+    return true;
+}
+
+}  // namespace rvn

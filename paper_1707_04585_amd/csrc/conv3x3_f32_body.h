@@ -112,16 +112,18 @@ struct Band {
         const int n = n0 + at.img, row = row0 - 1 + at.lr;
         const bool live = at.staging && n < s.N && row >= 0 && row < s.H;
         const uint32_t off = ((uint32_t)n * sn + (uint32_t)(row * s.W + 4 * at.q) + (uint32_t)at.cs * sch) * 4u;
-        const uint32_t base = (uint32_t)c0 * sch * 4u, step = (uint32_t)s.cpp * sch * 4u;
         const int left = min(kChunk, C - c0) - at.cs;
+        // (the scalar part of an offset stays inside the extent: the hardware takes it off before it compares)
 #pragma unroll
-        for (int i = 0; i < PASSES; ++i) g[i] = load4(in, live && i * s.cpp < left ? off : kNowhere, base + (uint32_t)i * step);
+        for (int i = 0; i < PASSES; ++i)
+            g[i] = load4(in, live && i * s.cpp < left ? off : kNowhere, (uint32_t)min(c0 + i * s.cpp, C - 1) * sch * 4u);
         if (BN && bn) {
 #pragma unroll
             for (int i = 0; i < PASSES; ++i) {
                 const uint32_t lane = live && i * s.cpp < left ? (uint32_t)at.cs * 4u : kNowhere;
-                sc[i] = load1(ss, lane, (uint32_t)(c0 + i * s.cpp) * 4u);
-                sh[i] = load1(ss, lane, (uint32_t)(C + c0 + i * s.cpp) * 4u);
+                const int c = min(c0 + i * s.cpp, C - 1);
+                sc[i] = load1(ss, lane, (uint32_t)c * 4u);
+                sh[i] = load1(ss, lane, (uint32_t)(C + c) * 4u);
             }
         }
     }
@@ -240,7 +242,7 @@ __device__ __forceinline__ void conv3x3_f32_body(const C3fArgs &p, int bx, int b
         for (int m = 0; m < MT; ++m)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                rv[m][j] = load4(r_rs, ok && ko_lane + m * 16 + j < p.CO ? r_off : kNowhere, (uint32_t)(co0 + m * 16 + j) * p.rsc * 4u);
+                rv[m][j] = load4(r_rs, ok && ko_lane + m * 16 + j < p.CO ? r_off : kNowhere, (uint32_t)min(co0 + m * 16 + j, p.CO - 1) * p.rsc * 4u);
     }
     zero_columns(p.s, smem, tid, kThreads);
     f4_t acc[MT][4];  // [.][pixel]: channels 4 * kq + 0 .. 3
@@ -289,7 +291,7 @@ __device__ __forceinline__ void conv3x3_f32_body(const C3fArgs &p, int bx, int b
 #pragma unroll
             for (int t = 0; t < 4; ++t) acc[m][t][j] = v[t];
             const bool has = ok && ko_lane + m * 16 + j < p.CO;
-            const uint32_t at = (uint32_t)(co0 + m * 16 + j) * p.osc * 4u;
+            const uint32_t at = (uint32_t)min(co0 + m * 16 + j, p.CO - 1) * p.osc * 4u;
             if (VEC) {
                 store4(o_rs, has ? o_off + at : kNowhere, v);
             } else {

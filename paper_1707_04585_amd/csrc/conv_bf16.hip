@@ -408,6 +408,7 @@ bool conv_bf16(Ctx &cx, View in, const float *scale_shift, const float *w, const
         if (conv1x1_bf16(cx, in, scale_shift, wq, ci, co, g, ep, r, out)) return true;
         wq = nullptr;  // ragged channels with images of 4 GiB or more: 64-bit offsets below, filter in its own layout
     }
+    if (ks == 3 && !transposed && conv3x3_bf16_narrow(cx, in, scale_shift, w, wq, ci, co, g, ep, r, out)) return true;
     if (ks == 3 && wq && conv3x3_bf16(cx, in, scale_shift, wq, ci, co, g, ep, r, out, scratch)) return true;
     const Bf16Plan pl = plan_bf16(ci, co, ks, g);
     if (!pl.ok) return false;

@@ -266,6 +266,11 @@ bool conv3x3_bf16_stride2(Ctx &cx, View in, const float *scale_shift, const uint
 bool conv3x3_bf16(Ctx &cx, View in, const float *scale_shift, const uint16_t *wq, int ci, int co, Geo g,
                   Epilogue ep, const View *r, View out, float *scratch);
 
+// The 3x3 convolution of narrow layers on bf16 operands (conv3x3_bf16_narrow.hip); wq as for conv3x3_bf16, or null: the filter is
+// converted where it is used.  Returns false (nothing launched) for the shapes it does not take.
+bool conv3x3_bf16_narrow(Ctx &cx, View in, const float *scale_shift, const float *w, const uint16_t *wq, int ci, int co, Geo g, Epilogue ep,
+                         const View *r, View out);
+
 PrepArgs plan_filter_prep(const FilterPrep *f, int count, Geo g, double *bytes);
 void prep_filters_bf16(Ctx &cx, const PrepArgs &a, double bytes);
 
