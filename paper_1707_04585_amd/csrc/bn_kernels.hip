@@ -624,6 +624,14 @@ void clear_counters(Ctx &cx, int *counters, int n) {
     cx.run(clear_counters_k, dim3((n + 255) / 256), dim3(256), 0, counters, n);
 }
 
+void bn_stats_merge(Ctx &cx, const StatsMerge &m, const PrepArgs *carry, double carry_bytes) {
+    if (!cx.launch(K_BN_STATS, 8.0 * (double)m.C * m.tiles + carry_bytes)) return;
+    PrepArgs pa{};
+    if (carry) pa = *carry;
+    cx.run(bn_stats_merge_k, dim3((unsigned)(m.C + pa.blocks)), dim3(kThreads), 0, m.partials, m.tiles, m.count, m.eps, m.gamma, m.beta,
+           m.stats, m.C, pa);
+}
+
 void bn_stats(Ctx &cx, View x, int c, Geo g, float eps, const float *gamma, const float *beta, float *scratch,
               int *counters, float *stats, const PrepArgs *carry, double carry_bytes) {
     // The convolution that wrote x may have left per-tile statistics of exactly this tensor.
@@ -631,11 +639,14 @@ void bn_stats(Ctx &cx, View x, int c, Geo g, float eps, const float *gamma, cons
     cx.emitted = EmittedStats{};
     if (e.p && cx.emit_buf && e.p == x.p && e.sn == x.sn && e.sc == x.sc && e.c == c && e.n == g.n && e.h == g.h &&
         e.w == g.w) {
-        if (!cx.launch(K_BN_STATS, 8.0 * (double)c * e.tiles + carry_bytes)) return;
-        PrepArgs pa{};
-        if (carry) pa = *carry;
-        cx.run(bn_stats_merge_k, dim3((unsigned)(c + pa.blocks)), dim3(kThreads), 0, (const float *)cx.emit_buf, e.tiles,
-               (float)e.count, eps, gamma, beta, stats, c, pa);
+        StatsMerge m;
+        m.partials = e.part ? e.part : cx.emit_buf;
+        m.tiles = e.tiles; m.count = (float)e.count; m.gamma = gamma; m.beta = beta; m.stats = stats; m.C = c; m.eps = eps; m.blocks = c;
+        if (cx.may_defer && !carry) {
+            cx.deferred = m;
+            return;
+        }
+        bn_stats_merge(cx, m, carry, carry_bytes);
         return;
     }
     const int S = reduce_splits(c, g);

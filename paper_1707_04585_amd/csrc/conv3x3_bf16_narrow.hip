@@ -29,10 +29,10 @@ namespace {
 
 using namespace c3n;
 
-template <int NT, int CH, int PASSES, bool GEN, bool EMIT, bool W32, int ORDER>
+template <int NT, int CH, int PASSES, bool GEN, bool EMIT, bool W32, int ORDER, bool MERGE>
 __global__ __launch_bounds__(kThreads, 2) void conv3x3_bf16_narrow_k(const C3nArgs p) {
     extern __shared__ __align__(16) char smem_c[];
-    conv3x3_bf16_narrow_body<NT, CH, PASSES, GEN, EMIT, W32, ORDER>(p, blockIdx.x, smem_c);
+    conv3x3_bf16_narrow_body<NT, CH, PASSES, GEN, EMIT, W32, ORDER, MERGE>(p, blockIdx.x, smem_c);
 }
 
 // Multiplier of fdiv_c3f: exact for e * d < 2^32 (e is a thread or block index here).
@@ -53,7 +53,7 @@ C3nPlan plan_c3n(const Geo &g, int slots, int ch) {
     for (int imgs = 1; imgs <= slots && imgs <= g.n; ++imgs) {
         for (int th = imgs > 1 ? g.h : 1; th <= g.h; ++th) {
             const int quads = imgs * th * wq, bquads = imgs * (th + 2) * wq, items = bquads * octs;
-            const size_t lds = ((size_t)imgs * (th + 2) * pitch + 1) * record_bytes(ch);
+            const size_t lds = ((size_t)imgs * (th + 2) * pitch + 1) * record_bytes(ch) + 2 * ch * 4;  // (and scale and shift)
             if (quads > slots || items > 2 * kThreads || lds > 64 * 1024) break;
             const int64_t bands = (g.h + th - 1) / th, blocks = bands * ((g.n + imgs - 1) / imgs);
             const double score = (double)g.n * g.h * wq / ((double)blocks * slots) - (items > kThreads ? 0.02 : 0.0);
@@ -105,15 +105,24 @@ struct C3nLaunch {
 
 template <int NT, int CH, int PASSES, int ORDER>
 void launch_converted(Ctx &cx, const C3nLaunch &L) {
-    if (L.gen) cx.run(conv3x3_bf16_narrow_k<NT, CH, PASSES, true, false, false, ORDER>, L.grid, dim3(kThreads), L.lds_bytes, L.a);
-    else if (L.a.emit) cx.run(conv3x3_bf16_narrow_k<NT, CH, PASSES, false, true, false, ORDER>, L.grid, dim3(kThreads), L.lds_bytes, L.a);
-    else cx.run(conv3x3_bf16_narrow_k<NT, CH, PASSES, false, false, false, ORDER>, L.grid, dim3(kThreads), L.lds_bytes, L.a);
+#define RVN_RUN(G_, E_, M_) cx.run(conv3x3_bf16_narrow_k<NT, CH, PASSES, G_, E_, false, ORDER, M_>, L.grid, dim3(kThreads), L.lds_bytes, L.a)
+    if constexpr (PASSES == 1) {
+        if (L.a.merge.blocks > 0) {
+            if (L.a.emit) RVN_RUN(false, true, true);
+            else RVN_RUN(false, false, true);
+            return;
+        }
+    }
+    if (L.gen) RVN_RUN(true, false, false);
+    else if (L.a.emit) RVN_RUN(false, true, false);
+    else RVN_RUN(false, false, false);
+#undef RVN_RUN
 }
 
 template <int NT, int CH, int PASSES>
 void launch_c3n(Ctx &cx, const C3nLaunch &L) {
     if (!L.a.wq) {
-        cx.run(conv3x3_bf16_narrow_k<NT, CH, PASSES, true, false, true, CH == 16 ? kChunks : kTaps>, L.grid, dim3(kThreads), L.lds_bytes, L.a);
+        cx.run(conv3x3_bf16_narrow_k<NT, CH, PASSES, true, false, true, CH == 16 ? kChunks : kTaps, false>, L.grid, dim3(kThreads), L.lds_bytes, L.a);
         return;
     }
     if constexpr (CH == 32) {
@@ -166,16 +175,38 @@ bool plan_launch(View in, const float *scale_shift, const float *w, const uint16
 
 }  // namespace
 
+// The merge in every workgroup costs reads of all partial results, against a launch of 3.8 to 4.7 us: 1.4 us for 16 KB (16
+// channels, 8 images of 32x32, 64 workgroups), 3.4 for 57 KB (56, 128 of 8x8, 128 workgroups; 4.1 saved); so 64 KB at most.  The
+// convolution's own partial results must find room beside them.
+bool conv3x3_bf16_narrow_merges(const Ctx &cx, int ci, int co, Geo g, const EmittedStats &e) {
+    const int cls = class_of(ci, co);
+    if (cls == 0 || e.count != 64 || e.tiles % 2 != 0 || e.tiles * cls > 8192 || ci % 8 != 0 || g.w % 4 != 0) return false;
+    return (size_t)(ci + co) * e.tiles * 2 <= cx.emit_floats;
+}
+
+bool conv3x3_bf16_narrow_takes(View in, const float *scale_shift, const float *w, const uint16_t *wq, int ci, int co, Geo g,
+                               Epilogue ep, const View *r, View out) {
+    C3nLaunch L;
+    return wq && plan_launch(in, scale_shift, w, wq, ci, co, g, ep, r, out, L) && L.passes == 1 && !L.gen;
+}
+
 bool conv3x3_bf16_narrow(Ctx &cx, View in, const float *scale_shift, const float *w, const uint16_t *wq, int ci, int co, Geo g, Epilogue ep,
                          const View *r, View out) {
     C3nLaunch L;
     if (!plan_launch(in, scale_shift, w, wq, ci, co, g, ep, r, out, L)) return false;
     const int tiles = (int)((int64_t)g.pixels() / 64);
+    float *emit = cx.emit_buf;
+    if (cx.deferred.blocks > 0) {  // (conv_fwd has made sure that this launch can merge)
+        L.a.merge = cx.deferred;
+        cx.deferred = StatsMerge{};
+        // partial results are read and written by one launch: not in the same place
+        if (emit && (size_t)(L.a.merge.partials - emit) < (size_t)co * tiles * 2) emit = const_cast<float *>(L.a.merge.partials) + (size_t)ci * L.a.merge.tiles * 2;
+    }
     // (not for ragged channel counts, as in conv1x1_bf16)
-    if (cx.want_emit && cx.emit_buf && !L.gen && L.whole && (size_t)co * tiles * 2 <= cx.emit_floats) {
-        L.a.emit = cx.emit_buf;
+    if (cx.want_emit && emit && !L.gen && L.whole && (size_t)(emit - cx.emit_buf) + (size_t)co * tiles * 2 <= cx.emit_floats) {
+        L.a.emit = emit;
         L.a.emit_tiles = tiles;
-        cx.emitted = EmittedStats{out.p, out.sn, out.sc, co, g.n, g.h, g.w, tiles, 64};
+        cx.emitted = EmittedStats{out.p, out.sn, out.sc, co, g.n, g.h, g.w, tiles, 64, emit};
     }
 #define RVN_CASE(NT_, CH_)                                                \
     if (L.cls == CH_ && L.nt == NT_) {                                    \

@@ -31,6 +31,9 @@ struct C3nArgs {
     // centred sum of squares of what is stored, at emit[(channel * emit_tiles + tile) * 2]
     float *emit;
     int emit_tiles;
+    // MERGE instances: the BN layer's statistics still lie in such partial results (of `in`); every workgroup merges them
+    // for itself, the first one also into stats [4][CI]
+    StatsMerge merge;
 };
 
 namespace {
@@ -85,10 +88,10 @@ struct QuadAt {
 // the tensor is loaded from kNowhere, which gives zero, with scale and shift zero as well (the scalar part of an offset stays
 // inside the extent, which the hardware takes it off).  GEN: rows that are not
 // whole quads, or a last octet of fewer channels.
-template <int CH, int PASSES, bool GEN>
+template <int CH, int PASSES, bool GEN, bool MERGE>
 struct Stage {
     f4_t g[PASSES][8], sc[PASSES][2], sh[PASSES][2];
-    int dst[PASSES], col[PASSES], left[PASSES];  // LDS bytes of the first pixel (-1: nothing); its column; channels from the octet on
+    int dst[PASSES], col[PASSES], left[PASSES], oct[PASSES];  // LDS bytes of the first pixel (-1: nothing); its column; channels from the octet on; the octet, -1 outside
 
     __device__ __forceinline__ void request(const C3nShape &s, int tid, __amdgpu_buffer_rsrc_t in, uint32_t sn, uint32_t sch,
                                             __amdgpu_buffer_rsrc_t ss, int C, int n0, int row0, bool bn) {
@@ -106,7 +109,8 @@ struct Stage {
             const uint32_t off = live ? ((uint32_t)n * sn + (uint32_t)(row * s.W + 4 * q) + (uint32_t)(8 * oc) * sch) * 4u : kNowhere;
 #pragma unroll
             for (int k = 0; k < 8; ++k) g[i][k] = load4(in, off, (uint32_t)min(k, C - 1) * sch * 4u);
-            if (bn) {
+            oct[i] = live ? oc : -1;
+            if (!MERGE && bn) {
                 const uint32_t at = live ? (uint32_t)oc * 32u : kNowhere;
                 const uint32_t at2 = live ? (uint32_t)(C + 8 * oc) * 4u : kNowhere;
 #pragma unroll
@@ -118,10 +122,21 @@ struct Stage {
         }
     }
     // a(x) = max(x*scale + shift, 0), or the values as they are, rounded into the pixels' records
-    __device__ __forceinline__ void commit(const C3nShape &s, char *lds, bool bn) {
+    // (MERGE: scale and shift from `ss`, [2][CH] in LDS)
+    __device__ __forceinline__ void commit(const C3nShape &s, char *lds, const float *ss, bool bn) {
 #pragma unroll
         for (int i = 0; i < PASSES; ++i) {
             if (dst[i] < 0) continue;
+            if (MERGE) {
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const f4_t zero = {0.f, 0.f, 0.f, 0.f};
+                    const int oc = max(oct[i], 0);
+                    sc[i][k] = *reinterpret_cast<const f4_t *>(ss + 8 * oc + 4 * k);
+                    sh[i][k] = *reinterpret_cast<const f4_t *>(ss + CH + 8 * oc + 4 * k);
+                    if (oct[i] < 0) sc[i][k] = sh[i][k] = zero;
+                }
+            }
             if (bn) {
 #pragma unroll
                 for (int k = 0; k < 8; ++k)
@@ -185,9 +200,64 @@ __device__ __forceinline__ void load_filter(__amdgpu_buffer_rsrc_t rs, const C3n
     }
 }
 
+__device__ __forceinline__ double shfl_xor_f64(double v, int mask) {
+    const int64_t b = __double_as_longlong(v);
+    const int lo = __shfl_xor((int)(b & 0xffffffff), mask, 64), hi = __shfl_xor((int)(b >> 32), mask, 64);
+    return __longlong_as_double(((int64_t)hi << 32) | (uint32_t)lo);
+}
+
+// The merge of bn_stats_merge_k by one workgroup for all of its channels: 256 / CH neighbouring lanes share a channel.  Equal
+// counts, so means are averaged (about the first one) instead of merged pair by pair; all in double.  Scale
+// and shift go to `ss` [2][CH].
+template <int CH>
+__device__ __forceinline__ void merge_statistics(const StatsMerge &m, float *ss, int tid, bool store) {
+    constexpr int T = kThreads / CH;
+    const int ch = tid / T, j = tid % T;
+    const bool has = ch < m.C;
+    const int c = has ? ch : 0;
+    const f4_t *const q = reinterpret_cast<const f4_t *>(m.partials) + (int64_t)c * (m.tiles / 2);
+    const float gamma = m.gamma[c], beta = m.beta[c];
+    const double pivot = (double)m.partials[(int64_t)c * m.tiles * 2];
+    double sum = 0.0, sq = 0.0, m2 = 0.0;
+    const int pairs = m.tiles / 2;
+    for (int t0 = j; t0 < pairs; t0 += 4 * T) {
+        f4_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = q[min(t0 + u * T, pairs - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool in = t0 + u * T < pairs;
+            const double d0 = in ? (double)v[u][0] - pivot : 0.0, d1 = in ? (double)v[u][2] - pivot : 0.0;
+            sum += d0 + d1;
+            sq += d0 * d0 + d1 * d1;
+            m2 += in ? (double)v[u][1] + (double)v[u][3] : 0.0;
+        }
+    }
+#pragma unroll
+    for (int off = T / 2; off > 0; off >>= 1) {
+        sum += shfl_xor_f64(sum, off);
+        sq += shfl_xor_f64(sq, off);
+        m2 += shfl_xor_f64(m2, off);
+    }
+    const double inv = 1.0 / m.tiles, mean = pivot + sum * inv;
+    const double var = (m2 / m.count + (sq - sum * sum * inv)) * inv;
+    const float mean_f = (float)mean, rstd_f = (float)(1.0 / sqrt(var + (double)m.eps));
+    const float scale = gamma * rstd_f, shift = fmaf(-mean_f, scale, beta);
+    if (j == 0) {
+        ss[ch] = has ? scale : 0.f;
+        ss[CH + ch] = has ? shift : 0.f;
+        if (store && has) {
+            m.stats[ch] = mean_f;
+            m.stats[m.C + ch] = rstd_f;
+            m.stats[2 * m.C + ch] = scale;
+            m.stats[3 * m.C + ch] = shift;
+        }
+    }
+}
+
 // Workgroup bx; `lds` is its dynamic LDS.  CH: channels of a record, and output channels at most.  A wavefront has one
 // tile of 32 output channels and NT of 32 pixels.
-template <int NT, int CH, int PASSES, bool GEN, bool EMIT, bool W32, int ORDER>
+template <int NT, int CH, int PASSES, bool GEN, bool EMIT, bool W32, int ORDER, bool MERGE>
 __device__ __forceinline__ void conv3x3_bf16_narrow_body(const C3nArgs &p, int bx, char *lds) {
     constexpr int WM = chan_waves(CH), WP = 4 / WM, KS = CH / 16, REC = record_bytes(CH);
     constexpr int KS1 = W32 || PASSES == 2 ? 1 : KS > 2 ? 2 : KS;  // filter chunks requested up front; the rest when the staging registers are free
@@ -200,7 +270,7 @@ __device__ __forceinline__ void conv3x3_bf16_narrow_body(const C3nArgs &p, int b
     const int n0 = img_grp * s.IMGS, row0 = band * s.TH;
     const bool bn = p.scale_shift != nullptr;
 
-    Stage<CH, PASSES, GEN> st;
+    Stage<CH, PASSES, GEN, MERGE> st;
     st.request(s, tid, rsrc(p.in, p.in_bytes), p.isn, p.isc, rsrc(bn ? p.scale_shift : p.in, bn ? (uint32_t)p.CI * 8u : 0u), p.CI, n0, row0, bn);
     const __amdgpu_buffer_rsrc_t w_rs = rsrc(W32 ? (const void *)p.w : (const void *)p.wq, p.w_bytes);
     bf16x8_t w[KS][9];
@@ -209,6 +279,8 @@ __device__ __forceinline__ void conv3x3_bf16_narrow_body(const C3nArgs &p, int b
 #pragma unroll
     for (int ks = 0; ks < KS1; ++ks) load_filter<W32>(w_rs, p, ko, ks, kg, w[ks]);
     zero_records<CH>(s, lds, tid);
+    float *const ss_lds = reinterpret_cast<float *>(lds + (s.IMGS * s.lrows * s.pitch + 1) * REC);
+    if constexpr (MERGE) merge_statistics<CH>(p.merge, ss_lds, tid, bx == 0);
 
     // ---- where this lane's results go (channel ko; four consecutive pixels per register quad) and its skip values, all
     //      requested before the first store: r may alias out element for element
@@ -245,7 +317,8 @@ __device__ __forceinline__ void conv3x3_bf16_narrow_body(const C3nArgs &p, int b
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[h][t][i] = 0.f;
 
-    st.commit(s, lds, bn);
+    if (MERGE) __syncthreads();  // scale and shift are there
+    st.commit(s, lds, ss_lds, bn);
 #pragma unroll
     for (int ks = KS1; ks < KS; ++ks) load_filter<W32>(w_rs, p, ko, ks, kg, w[ks]);
     __syncthreads();

@@ -202,6 +202,10 @@ bool conv_mfma_plan(View in, const float *scale_shift, const float *w, bool tran
 
 void conv_fwd(Ctx &cx, View x, const float *scale_shift, rvn_dtype dt, const float *w, const uint16_t *wq, int cin,
               int cout, int ks, Geo g, Epilogue ep, const View *r, View out, float *scratch) {
+    if (cx.deferred.blocks > 0 && !(dt == RVN_BF16 && ks == 3 && conv3x3_bf16_narrow_takes(x, scale_shift, w, wq, cin, cout, g, ep, r, out))) {
+        bn_stats_merge(cx, cx.deferred);
+        cx.deferred = StatsMerge{};
+    }
     const double P = (double)g.pixels();
     const double flops = 2.0 * P * cin * cout * ks * ks;
     cx.cost.conv_fwd_calls += 1;

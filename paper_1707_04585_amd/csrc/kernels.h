@@ -67,6 +67,7 @@ struct EmittedStats {
     int c = 0, n = 0, h = 0, w = 0;
     int tiles = 0;  // partial results per channel: partials[(channel * tiles + tile) * 2 + {0, 1}]
     int count = 0;  // pixels behind every partial result
+    const float *part = nullptr;  // where they are; null: at the start of the lent buffer
 };
 
 // The filter w [cout][cin][ks][ks] in bf16 and in the order the bf16 kernel
@@ -130,6 +131,10 @@ struct Ctx {
     float *emit_buf = nullptr;
     size_t emit_floats = 0;
     bool want_emit = false;
+    // A merge that the next conv_fwd call may do in its own launch (bn_stats leaves it here, with nothing launched, where
+    // the driver has said through `may_defer` which convolution follows); conv_fwd launches it if it cannot.
+    bool may_defer = false;
+    StatsMerge deferred;
     EmittedStats emitted;
     hipStream_t stream = nullptr;
     bool dry = false;
@@ -213,6 +218,9 @@ struct PrepArgs;
 void bn_stats(Ctx &cx, View x, int c, Geo g, float eps, const float *gamma, const float *beta,
               float *scratch, int *counters, float *stats, const PrepArgs *carry = nullptr, double carry_bytes = 0.0);
 
+// The launch that merges partial statistics (what bn_stats does where it has them and defers nothing).
+void bn_stats_merge(Ctx &cx, const StatsMerge &m, const PrepArgs *carry = nullptr, double carry_bytes = 0.0);
+
 // Zero n ticket counters (once per library call; the workspace is caller
 // memory with unknown contents).
 void clear_counters(Ctx &cx, int *counters, int n);
@@ -268,6 +276,11 @@ bool conv3x3_bf16(Ctx &cx, View in, const float *scale_shift, const uint16_t *wq
 
 // The 3x3 convolution of narrow layers on bf16 operands (conv3x3_bf16_narrow.hip); wq as for conv3x3_bf16, or null: the filter is
 // converted where it is used.  Returns false (nothing launched) for the shapes it does not take.
+// It can also do the merge of the statistics it reads, from partial results `e` of its input (cx.deferred): whether that
+// pays at these sizes, and whether the kernel takes exactly this call.
+bool conv3x3_bf16_narrow_merges(const Ctx &cx, int ci, int co, Geo g, const EmittedStats &e);
+bool conv3x3_bf16_narrow_takes(View in, const float *scale_shift, const float *w, const uint16_t *wq, int ci, int co, Geo g,
+                               Epilogue ep, const View *r, View out);
 bool conv3x3_bf16_narrow(Ctx &cx, View in, const float *scale_shift, const float *w, const uint16_t *wq, int ci, int co, Geo g, Epilogue ep,
                          const View *r, View out);
 

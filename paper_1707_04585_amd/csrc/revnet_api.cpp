@@ -333,8 +333,10 @@ const float *func_forward(Ctx &cx, const rvn_block_desc &d, const Plan &pl, cons
         if (l == 0 && ahead) {
             cx.emitted = EmittedStats{};  // (the filters were converted in the launch that merged the statistics)
         } else {
+            cx.may_defer = d.conv_dtype == RVN_BF16 && ly.ks == 3 && conv3x3_bf16_narrow_merges(cx, ly.cin, ly.cout, g, cx.emitted);
             bn_stats(cx, cur, ly.cin, g, d.bn_eps, p.bn_gamma[l], p.bn_beta[l], b.bn_scratch, b.counters, b.stats[l],
                      l == 0 && pa.jobs > 0 ? &pa : nullptr, l == 0 ? prep_bytes : 0.0);
+            cx.may_defer = false;
         }
         const float *scale_shift = (l == 0 ? stats0 : b.stats[l]) + 2 * ly.cin;
         if (l < pl.L - 1) {
@@ -370,7 +372,7 @@ void arm_merge(Ctx &cx, const rvn_block_desc &d, const Plan &pl, const Bufs &b, 
     float *const slot = b.stats_in[cx.premerge_slot];
     cx.premerge_slot ^= 1;
     StatsMerge m;
-    m.partials = cx.emit_buf;
+    m.partials = e.part ? e.part : cx.emit_buf;
     m.tiles = e.tiles;
     m.count = (float)e.count;
     m.gamma = consumer.bn_gamma[0];
