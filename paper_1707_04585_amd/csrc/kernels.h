@@ -277,8 +277,9 @@ bool conv3x3_bf16(Ctx &cx, View in, const float *scale_shift, const uint16_t *wq
 // The 3x3 convolution of narrow layers on bf16 operands (conv3x3_bf16_narrow.hip); wq as for conv3x3_bf16, or null: the filter is
 // converted where it is used.  Returns false (nothing launched) for the shapes it does not take.
 // It can also do the merge of the statistics it reads, from partial results `e` of its input (cx.deferred): whether that
-// pays at these sizes, and whether the kernel takes exactly this call.
+// pays at these sizes, also with a filter that nobody has converted, and whether the kernel takes exactly this call.
 bool conv3x3_bf16_narrow_merges(const Ctx &cx, int ci, int co, Geo g, const EmittedStats &e);
+bool conv3x3_bf16_narrow_unconverted(const Ctx &cx, int ci, int co, Geo g, const EmittedStats &e);
 bool conv3x3_bf16_narrow_takes(View in, const float *scale_shift, const float *w, const uint16_t *wq, int ci, int co, Geo g,
                                Epilogue ep, const View *r, View out);
 bool conv3x3_bf16_narrow(Ctx &cx, View in, const float *scale_shift, const float *w, const uint16_t *wq, int ci, int co, Geo g, Epilogue ep,

@@ -327,9 +327,14 @@ const float *func_forward(Ctx &cx, const rvn_block_desc &d, const Plan &pl, cons
         prep[l] = FilterPrep{p.conv_w[l], pl.layers[l].cin, pl.layers[l].cout, pl.layers[l].ks, b.wq_f[l], b.wq_b[l]};
     // The conversion rides in the first statistics launch of the function.
     double prep_bytes = 0.0;
-    const PrepArgs pa = plan_filter_prep(prep, pl.L, g, &prep_bytes);
+    // A forward pass of small narrow layers does without: the launch that would carry it is then not needed.
+    bool convert = !(ep == EP_ADD && d.conv_dtype == RVN_BF16 && !ahead && cx.emitted.p == x.p);
+    for (int l = 0; l < pl.L && !convert; ++l)
+        convert = pl.layers[l].ks != 3 || !conv3x3_bf16_narrow_unconverted(cx, pl.layers[l].cin, pl.layers[l].cout, g, cx.emitted);
+    const PrepArgs pa = convert ? plan_filter_prep(prep, pl.L, g, &prep_bytes) : PrepArgs{};
     for (int l = 0; l < pl.L; ++l) {
         const Layer &ly = pl.layers[l];
+        const uint16_t *const wq = convert ? b.wq_f[l] : nullptr;
         if (l == 0 && ahead) {
             cx.emitted = EmittedStats{};  // (the filters were converted in the launch that merged the statistics)
         } else {
@@ -341,18 +346,18 @@ const float *func_forward(Ctx &cx, const rvn_block_desc &d, const Plan &pl, cons
         const float *scale_shift = (l == 0 ? stats0 : b.stats[l]) + 2 * ly.cin;
         if (l < pl.L - 1) {
             View h = dense_view(b.h[l], ly.cout, g);
-            conv_fwd(cx, cur, scale_shift, d.conv_dtype, p.conv_w[l], b.wq_f[l], ly.cin, ly.cout, ly.ks, g, EP_STORE, nullptr, h, b.conv_scratch);
+            conv_fwd(cx, cur, scale_shift, d.conv_dtype, p.conv_w[l], wq, ly.cin, ly.cout, ly.ks, g, EP_STORE, nullptr, h, b.conv_scratch);
             cur = h;
         } else if (frac_bits) {
             // (no statistics from this epilogue: the next BN layer reads the stream's fp32 copy, not fout)
             float *const lent = cx.emit_buf;
             cx.emit_buf = nullptr;
-            conv_fwd(cx, cur, scale_shift, d.conv_dtype, p.conv_w[l], b.wq_f[l], ly.cin, ly.cout, ly.ks, g, EP_STORE, nullptr,
+            conv_fwd(cx, cur, scale_shift, d.conv_dtype, p.conv_w[l], wq, ly.cin, ly.cout, ly.ks, g, EP_STORE, nullptr,
                      dense_view(b.fout, ly.cout, g), b.conv_scratch);
             cx.emit_buf = lent;
             fix_axpy(cx, *r, b.fout, ly.cout, g, frac_bits, ep == EP_SUB ? -1 : 1, out);
         } else {
-            conv_fwd(cx, cur, scale_shift, d.conv_dtype, p.conv_w[l], b.wq_f[l], ly.cin, ly.cout, ly.ks, g, ep, r, out, b.conv_scratch);
+            conv_fwd(cx, cur, scale_shift, d.conv_dtype, p.conv_w[l], wq, ly.cin, ly.cout, ly.ks, g, ep, r, out, b.conv_scratch);
         }
     }
     return stats0;
