@@ -361,7 +361,9 @@ __device__ __forceinline__ void conv3x3_bf16_narrow_body(const C3nArgs &p, int b
         }
     // Statistics of what was stored, for the BN layer that reads it next: per channel and 64 consecutive pixels, sums of
     // (v - pivot) and (v - pivot)^2, pivot = the first value.  The order is that of the kernels that take the layer at
-    // other sizes (pixel p and p + 32, then halves down to neighbours), so a tensor's statistics are the same bits.
+    // other sizes (pixel p and p + 32, then halves down to neighbours; the compiler contracts their first sum of squares,
+    // also the one across lanes in the kernel that sums a split layer, to the fma below), so a tensor's statistics
+    // are the same bits.
     if constexpr (EMIT) {
         float hi[16];  // the later 32 pixels of the 64 that this lane sums
         if constexpr (NT == 2) {
@@ -390,12 +392,7 @@ __device__ __forceinline__ void conv3x3_bf16_narrow_body(const C3nArgs &p, int b
         for (int i = 0; i < 16; ++i) {
             const float d0 = acc[0][0][i] - pivot, d1 = hi[i] - pivot;
             ea[i] = d0 + d1;
-            if constexpr (ORDER == kHalves) {  // (the kernel that sums a split layer adds rounded squares)
-#pragma clang fp contract(off)
-                eb[i] = d0 * d0 + d1 * d1;
-            } else {
-                eb[i] = fmaf(d1, d1, d0 * d0);
-            }
+            eb[i] = fmaf(d0, d0, d1 * d1);
         }
         // register i of a lane is pixel 8 * (i / 4) + 4 * kg + i % 4
 #pragma unroll

@@ -1,8 +1,10 @@
 """bf16 3x3 layers of up to 64 channels, at the sizes where the pixel blocks, staging passes, channel octets and channel
 classes of their kernels end, against the oracle with operands rounded to bf16; the check, its bars and the infinities
 next to the tensors are those of the ragged-channel layers."""
+import numpy as np
 import pytest
 
+import synth_inputs as S
 import test_gpu_ragged_channels as R
 
 pytestmark = pytest.mark.gpu
@@ -34,3 +36,36 @@ CASES = [
 @pytest.mark.parametrize("case", CASES, ids=lambda k: "n%d c%d %dx%d" % (k["n"], k["c"], k["h"], k["w"]))
 def test_block(case):
     R.test_block(dict(kind="basic", **case))
+
+
+SAME_BITS = [
+    # (images, channels, rows, columns); blocks that are whole, so that both kernels leave statistics
+    (33, 16, 32, 32), (24, 16, 8, 8), (140, 16, 32, 32), (33, 32, 16, 16), (300, 32, 16, 16), (40, 48, 16, 16), (20, 40, 32, 32),
+    (64, 56, 8, 8), (33, 64, 16, 16), (20, 64, 32, 32),
+]
+
+
+@pytest.mark.parametrize("shape", SAME_BITS, ids=lambda k: "n%d c%d %dx%d" % k)
+def test_forward_bits_are_those_of_the_wider_kernels(shape):
+    """Sums and statistics keep the order of the kernels that take the layer where this one does not: tensors that end just
+    short of 4 GiB, which only those take, give the same bits as dense ones."""
+    import torch
+    import paper_1707_04585_amd as rv
+    from paper_1707_04585_amd.torch_harness import StackRunner
+    n, ch, h, w = shape
+    cfg = dict(kind="basic", n=n, c=2 * ch, h=h, w=w, width=None, depth=2, conv="bf16", affine="random")
+    x, params, _ = S.draw_stack(S.BASE_SEED + 1619, **cfg)
+    r = StackRunner(**cfg)
+    r.set_params(params)
+    full = torch.as_tensor(x.astype(np.float32)).to(r.device)
+    dense, far = 2 * ch * h * w, ((1 << 30) - 2 * ch * h * w) // n // 4 * 4 - 4
+    assert (n - 1) * far * 4 > 0xf0000000 and (n * far + ch * h * w) * 4 < 1 << 32
+    got = []
+    for sn in (dense, far):
+        both = torch.empty((n - 1) * sn + dense, dtype=torch.float32, device=r.device).as_strided((n, 2 * ch, h, w), (sn, h * w, w, 1))
+        both.copy_(full)
+        X = [both[:, :ch], both[:, ch:]]
+        rv.revnet_stack_fwd(r.desc, 2, *X, r.params, *X, r.ws)
+        torch.cuda.synchronize()
+        got.append(both.cpu().numpy())
+    np.testing.assert_array_equal(got[0], got[1])
