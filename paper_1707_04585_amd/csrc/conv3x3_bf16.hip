@@ -195,6 +195,11 @@ void launch_c3(Ctx &cx, const C3Launch &L, dim3 grid) {
 
 bool conv3x3_bf16_ok(int ci, int co, const Geo &g) { return plan_c3(ci, co, g).ok; }
 
+Conv3x3Bf16Form conv3x3_bf16_form(int ci, int co, const Geo &g) {
+    const C3Plan pl = plan_c3(ci, co, g);
+    return pl.ok ? Conv3x3Bf16Form{pl.KC, pl.S} : Conv3x3Bf16Form{0, 1};
+}
+
 size_t conv3x3_bf16_scratch_floats(int ci, int co, const Geo &g, int stride) {
     const C3Plan pl = plan_c3(ci, co, g, stride);
     return pl.ok && pl.S > 1 ? (size_t)pl.S * g.n * co * (g.h / stride) * (g.w / stride) : 0;

@@ -12,8 +12,8 @@
 //    consecutive pixels of one channel: 16-byte stores, and statistics that need few shuffles;
 //  * blocks shrink (256 to 64 pixels) until every compute unit has one, instead of a split of the channels with a second
 //    launch that sums it.
-// Sums and statistics keep the order of conv3x3_bf16 (Order in conv3x3_bf16_narrow_body.h), so a layer's results do not depend on which of the two
-// kernels its size goes to.
+// Sums and statistics keep the order of the kernel that would take the layer otherwise, conv3x3_bf16 or the general one
+// (Order in conv3x3_bf16_narrow_body.h): its results are the same bits.
 // Measured, forward launch with statistics (register-tiled kernel before): 16 -> 16 channels, 8 images of 32x32 8.8 -> 4.7 us,
 // 128 images 13.0 -> 8.4; 32 -> 32, 128 of 16x16 12.5 -> 6.6; 56 -> 56, 128 of 8x8 10.8 + 4.2 (sum of the split) -> 6.6.
 // With v_mfma_f32_16x16x32_bf16 (two taps of 16 channels an instruction, blocks down to 64 pixels) the 16-channel launches took
@@ -103,36 +103,45 @@ struct C3nLaunch {
     size_t lds_bytes;
 };
 
-template <int NT, int CH, int PASSES, int ORDER, bool W32 = false>
+template <int NT, int CH, int PASSES, int ORDER, bool W32 = false, bool GEN_ONLY = false>
 void launch_order(Ctx &cx, const C3nLaunch &L) {
 #define RVN_RUN(G_, E_, M_) cx.run(conv3x3_bf16_narrow_k<NT, CH, PASSES, G_, E_, W32, ORDER, M_>, L.grid, dim3(kThreads), L.lds_bytes, L.a)
-    if constexpr (PASSES == 1) {
-        if (L.a.merge.blocks > 0) {
-            if (L.a.emit) RVN_RUN(false, true, true);
-            else RVN_RUN(false, false, true);
-            return;
+    if constexpr (GEN_ONLY) {
+        RVN_RUN(true, false, false);
+    } else {
+        if constexpr (PASSES == 1) {
+            if (L.a.merge.blocks > 0) {
+                if (L.a.emit) RVN_RUN(false, true, true);
+                else RVN_RUN(false, false, true);
+                return;
+            }
         }
+        if (L.gen) RVN_RUN(true, false, false);
+        else if (L.a.emit) RVN_RUN(false, true, false);
+        else RVN_RUN(false, false, false);
     }
-    if (L.gen) RVN_RUN(true, false, false);
-    else if (L.a.emit) RVN_RUN(false, true, false);
-    else RVN_RUN(false, false, false);
 #undef RVN_RUN
 }
 
+// More than 16 channels: a filter that has not been converted, and the general kernel's chunk of 64, come with ragged
+// channel counts or rows only, the chunk of 32 in the 64-channel class too (32 channels that become more are a
+// subsampling block's, which has a strided kernel).
 template <int NT, int CH, int PASSES>
 void launch_c3n(Ctx &cx, const C3nLaunch &L) {
-    if (!L.a.wq) {
-        if constexpr (CH == 16) launch_order<NT, CH, PASSES, kChunks, true>(cx, L);
-        else cx.run(conv3x3_bf16_narrow_k<NT, CH, PASSES, true, false, true, kTaps, false>, L.grid, dim3(kThreads), L.lds_bytes, L.a);
-        return;
+    if constexpr (CH == 16) {
+        if (L.a.wq) launch_order<NT, CH, PASSES, kChunk16>(cx, L);
+        else launch_order<NT, CH, PASSES, kChunk16, true>(cx, L);
+    } else {
+        if constexpr (CH == 64) {
+            if (L.order == kHalves) return launch_order<NT, CH, PASSES, kHalves>(cx, L);
+            if (L.order == kChunk64)
+                return L.a.wq ? launch_order<NT, CH, PASSES, kChunk64, false, true>(cx, L) : launch_order<NT, CH, PASSES, kChunk64, true, true>(cx, L);
+        }
+        if (L.order == kChunk32)
+            return L.a.wq ? launch_order<NT, CH, PASSES, kChunk32, false, CH == 64>(cx, L) : launch_order<NT, CH, PASSES, kChunk32, true, true>(cx, L);
+        if (L.a.wq) launch_order<NT, CH, PASSES, kChunk16>(cx, L);
+        else launch_order<NT, CH, PASSES, kChunk16, true, true>(cx, L);
     }
-    if constexpr (CH == 32) {
-        if (L.order == kTaps) return launch_order<NT, CH, PASSES, kTaps>(cx, L);
-    }
-    if constexpr (CH == 64) {
-        if (L.order == kHalves) return launch_order<NT, CH, PASSES, kHalves>(cx, L);
-    }
-    launch_order<NT, CH, PASSES, kChunks>(cx, L);
 }
 
 bool plan_launch(View in, const float *scale_shift, const float *w, const uint16_t *wq, int ci, int co, Geo g, Epilogue ep,
@@ -167,14 +176,31 @@ bool plan_launch(View in, const float *scale_shift, const float *w, const uint16
     L.gen = g.w % 4 != 0 || ci % 8 != 0 || (!wq && L.cls != 16);
     L.whole = g.w % 4 == 0 && pl.s.quads == 8 * L.nt * wp && g.n % pl.s.IMGS == 0 && g.h % pl.s.TH == 0;
     L.passes = pl.passes;
-    // (the sums of conv3x3_bf16: chunks of 16 channels, or of 32 where that is all, in two partial results where it splits)
-    L.order = ci == 32 ? kTaps : conv3x3_bf16_scratch_floats(ci, co, g) > 0 ? kHalves : kChunks;
+    const Conv3x3Bf16Form form = conv3x3_bf16_form(ci, co, g);
+    if (wq && form.chunk > 0) L.order = form.parts > 1 ? kHalves : form.chunk / 16;
+    else L.order = std::max(16, conv_bf16_chunk(ci, co, 3, g)) / 16;
+    // (64-channel class: no caller has these, see launch_c3n)
+    if (L.cls > 16 && !L.gen && (L.order == kChunk64 || (L.cls == 64 && L.order == kChunk32))) return false;
     L.grid = dim3((unsigned)pl.blocks);
     L.lds_bytes = pl.lds_bytes;
     return true;
 }
 
 }  // namespace
+
+// How a layer of dense tensors runs, for the tests: class (16, 32 or 64 channels), 32-pixel tiles a wavefront has, staging passes,
+// whether the rows or channels are ragged, Order, whether every block is whole; in hexadecimal digits pairs from the
+// class down, or -1 (another kernel).
+extern "C" int64_t rvn_conv3x3_bf16_narrow_form(int ci, int co, int n, int h, int w, int converted) {
+    const Geo g{n, h, w};
+    const uint16_t wq = 0;
+    float f = 0.f;
+    C3nLaunch L;
+    if (!plan_launch(dense_view(&f, ci, g), &f, &f, converted ? &wq : nullptr, ci, co, g, EP_STORE, nullptr, dense_view(&f, co, g), L)) return -1;
+    int64_t form = 0;
+    for (int v : {L.cls, L.nt, L.passes, (int)L.gen, L.order, (int)L.whole}) form = form * 256 + v;
+    return form;
+}
 
 // The merge in every workgroup costs reads of all partial results, against a launch of 3.8 to 4.7 us: 1.4 us for 16 KB (16
 // channels, 8 images of 32x32, 64 workgroups), 3.4 for 57 KB (56, 128 of 8x8, 128 workgroups; 4.1 saved); so 64 KB at most.  The

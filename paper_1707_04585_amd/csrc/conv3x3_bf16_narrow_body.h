@@ -60,9 +60,9 @@ constexpr int kThreads = 256;
 constexpr int record_bytes(int ch) { return ch * 2 + 16; }
 constexpr int chan_waves(int ch) { return ch == 64 ? 2 : 1; }  // wavefronts side by side along the output channels
 
-// Order of a result's sum, that of the kernels that take the layer at other sizes: 16 channels at a time and the taps
-// of each, the taps and the channels of each, or two chains of half the channels.
-enum Order { kChunks = 0, kTaps = 1, kHalves = 2 };
+// Order of a result's sum, that of the kernels that take the layer at other sizes: chunks of 16, 32 or 64 channels, in each
+// the taps, and for every tap the chunk's channels; or two chains of half the channels in chunks of 16.
+enum Order { kChunk16 = 1, kChunk32 = 2, kChunk64 = 4, kHalves = 0 };
 
 __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
     const float2_t v = {lo, hi};
@@ -325,7 +325,8 @@ __device__ __forceinline__ void conv3x3_bf16_narrow_body(const C3nArgs &p, int b
     const int row_bytes = s.pitch * REC;
 #pragma unroll
     for (int i = 0; i < 9 * KS; ++i) {
-        const int tap = ORDER == kTaps ? i / KS : i % 9, ks = ORDER == kTaps ? i % KS : i / 9;
+        constexpr int CS = ORDER == kHalves ? 1 : ORDER;  // 16-channel steps of a chunk
+        const int chunk = i / (9 * CS), tap = i % (9 * CS) / CS, ks = chunk * CS + i % CS;
         const int h = ORDER == kHalves && ks >= 2 ? 1 : 0;
         bf16x8_t a[NT];
 #pragma unroll

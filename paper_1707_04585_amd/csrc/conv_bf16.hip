@@ -353,6 +353,11 @@ bool conv1x1_staged_better(int ci, int co, const Geo &g) {
     return pl.ok && pl.MT == 1 && pl.NT == 1 && pl.KC >= ci;
 }
 
+int conv_bf16_chunk(int ci, int co, int ks, const Geo &g) {
+    const Bf16Plan pl = plan_bf16(ci, co, ks, g);
+    return pl.ok ? pl.KC : 0;
+}
+
 size_t conv_bf16_scratch_floats(int ci, int co, int ks, const Geo &g) {
     return ks == 3 ? conv3x3_bf16_scratch_floats(ci, co, g) : 0;
 }

@@ -274,6 +274,14 @@ bool conv3x3_bf16_stride2(Ctx &cx, View in, const float *scale_shift, const uint
 bool conv3x3_bf16(Ctx &cx, View in, const float *scale_shift, const uint16_t *wq, int ci, int co, Geo g,
                   Epilogue ep, const View *r, View out, float *scratch);
 
+// How conv3x3_bf16 forms a result, where it takes the layer: input channels of a chunk (0: not taken), and in how many
+// parts, each a launch's own sum, they are split; and the chunk of the general kernel (0: no tiling).
+struct Conv3x3Bf16Form {
+    int chunk, parts;
+};
+Conv3x3Bf16Form conv3x3_bf16_form(int ci, int co, const Geo &g);
+int conv_bf16_chunk(int ci, int co, int ks, const Geo &g);
+
 // The 3x3 convolution of narrow layers on bf16 operands (conv3x3_bf16_narrow.hip); wq as for conv3x3_bf16, or null: the filter is
 // converted where it is used.  Returns false (nothing launched) for the shapes it does not take.
 // It can also do the merge of the statistics it reads, from partial results `e` of its input (cx.deferred): whether that
