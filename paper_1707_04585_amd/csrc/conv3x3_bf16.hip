@@ -151,6 +151,9 @@ C3Plan plan_c3(int ci, int co, const Geo &g, int stride = 1) {
     return pl;
 }
 
+// Whether the wavefronts of the kernel that sums a split layer are whole runs of 64 pixels of one plane.
+bool sum_emits(int co, const Geo &g) { return g.hw() % 64 == 0 && g.pixels() * co % kThreads == 0; }
+
 // More than 64 KB of dynamic LDS has to be asked for, once per kernel.
 template <typename K>
 bool raise_lds_limit(Ctx &cx, K kernel, bool &raised) {
@@ -197,7 +200,7 @@ bool conv3x3_bf16_ok(int ci, int co, const Geo &g) { return plan_c3(ci, co, g).o
 
 Conv3x3Bf16Form conv3x3_bf16_form(int ci, int co, const Geo &g) {
     const C3Plan pl = plan_c3(ci, co, g);
-    return pl.ok ? Conv3x3Bf16Form{pl.KC, pl.S} : Conv3x3Bf16Form{0, 1};
+    return pl.ok ? Conv3x3Bf16Form{pl.KC, pl.S, pl.S > 1 && sum_emits(co, g)} : Conv3x3Bf16Form{0, 1, false};
 }
 
 size_t conv3x3_bf16_scratch_floats(int ci, int co, const Geo &g, int stride) {
@@ -254,8 +257,7 @@ void conv3x3_bf16_finish(Ctx &cx, const C3Launch &L, Geo g) {
     const dim3 rgrid((unsigned)((total + kThreads - 1) / kThreads));
     // (a launch of its own in the accounts; the convolution's algorithmic bytes were counted with the first)
     const bool go = cx.launch(K_SPLITK_REDUCE, 0.0);
-    if (cx.want_emit && cx.emit_buf && hw % 64 == 0 && total % kThreads == 0 &&
-        (size_t)co * rtiles * 2 <= cx.emit_floats) {
+    if (cx.want_emit && cx.emit_buf && sum_emits(co, g) && (size_t)co * rtiles * 2 <= cx.emit_floats) {
         cx.emitted = EmittedStats{a.out, a.osn, a.osc, co, g.n, g.h, g.w, rtiles, 64};
         if (go)
             cx.run(splitk_reduce_k<true>, rgrid, dim3(kThreads), 0, L.scratch, a.part_stride, L.S, co, hw, total, a.r,

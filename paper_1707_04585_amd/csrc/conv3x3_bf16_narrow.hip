@@ -13,7 +13,10 @@
 //  * blocks shrink (256 to 64 pixels) until every compute unit has one, instead of a split of the channels with a second
 //    launch that sums it.
 // Sums and statistics keep the order of the kernel that would take the layer otherwise, conv3x3_bf16 or the general one
-// (Order in conv3x3_bf16_narrow_body.h): its results are the same bits.
+// (Order in conv3x3_bf16_narrow_body.h): its results are the same bits, and so are those of the layers behind it.  Where
+// blocks are not whole tiles of 64 pixels and that kernel would have left statistics, the pass over the tensor forms them
+// in its order (bn_stats_tiles_k).  Where that kernel leaves none and this one does, they come from tiles of 64 pixels
+// merged in double instead of fp32 sums over whole images: other roundings.
 // Measured, forward launch with statistics (register-tiled kernel before): 16 -> 16 channels, 8 images of 32x32 8.8 -> 4.7 us,
 // 128 images 13.0 -> 8.4; 32 -> 32, 128 of 16x16 12.5 -> 6.6; 56 -> 56, 128 of 8x8 10.8 + 4.2 (sum of the split) -> 6.6.
 // With v_mfma_f32_16x16x32_bf16 (two taps of 16 channels an instruction, blocks down to 64 pixels) the 16-channel launches took
@@ -98,7 +101,7 @@ bool takes(int cls, bool converted, const Geo &g) {
 struct C3nLaunch {
     C3nArgs a;
     int cls, nt, passes, order;  // cls: 16, 32 or 64 channels
-    bool gen, whole;
+    bool gen, whole, owes;       // owes: leaves no statistics where conv3x3_bf16 would
     dim3 grid;
     size_t lds_bytes;
 };
@@ -179,6 +182,7 @@ bool plan_launch(View in, const float *scale_shift, const float *w, const uint16
     const Conv3x3Bf16Form form = conv3x3_bf16_form(ci, co, g);
     if (wq && form.chunk > 0) L.order = form.parts > 1 ? kHalves : form.chunk / 16;
     else L.order = std::max(16, conv_bf16_chunk(ci, co, 3, g)) / 16;
+    L.owes = wq && form.sum_emits && !(L.whole && !L.gen);
     // (64-channel class: no caller has these, see launch_c3n)
     if (L.cls > 16 && !L.gen && (L.order == kChunk64 || (L.cls == 64 && L.order == kChunk32))) return false;
     L.grid = dim3((unsigned)pl.blocks);
@@ -207,7 +211,7 @@ extern "C" int64_t rvn_conv3x3_bf16_narrow_form(int ci, int co, int n, int h, in
 // convolution's own partial results must find room beside them.
 bool conv3x3_bf16_narrow_merges(const Ctx &cx, int ci, int co, Geo g, const EmittedStats &e) {
     const int cls = class_of(ci, co);
-    if (cls == 0 || e.count != 64 || e.tiles % 2 != 0 || e.tiles * cls > 8192 || ci % 8 != 0 || g.w % 4 != 0) return false;
+    if (cls == 0 || e.to_come || e.count != 64 || e.tiles % 2 != 0 || e.tiles * cls > 8192 || ci % 8 != 0 || g.w % 4 != 0) return false;
     return (size_t)(ci + co) * e.tiles * 2 <= cx.emit_floats;
 }
 
@@ -241,6 +245,10 @@ bool conv3x3_bf16_narrow(Ctx &cx, View in, const float *scale_shift, const float
         L.a.emit = emit;
         L.a.emit_tiles = tiles;
         cx.emitted = EmittedStats{out.p, out.sn, out.sc, co, g.n, g.h, g.w, tiles, 64, emit};
+    } else if (cx.want_emit && cx.emit_buf && L.owes && (size_t)co * tiles * 2 <= cx.emit_floats) {
+        // Blocks that are not whole tiles, in a layer whose tiles the split launch would have left: they come from the
+        // statistics pass, so that the layers behind see the same bits.
+        cx.emitted = EmittedStats{out.p, out.sn, out.sc, co, g.n, g.h, g.w, tiles, 64, nullptr, true};
     }
 #define RVN_CASE(NT_, CH_)                                                \
     if (L.cls == CH_ && L.nt == NT_) {                                    \

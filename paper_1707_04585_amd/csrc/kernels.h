@@ -68,6 +68,7 @@ struct EmittedStats {
     int tiles = 0;  // partial results per channel: partials[(channel * tiles + tile) * 2 + {0, 1}]
     int count = 0;  // pixels behind every partial result
     const float *part = nullptr;  // where they are; null: at the start of the lent buffer
+    bool to_come = false;  // nothing is there: the statistics pass over the tensor is to form these partial results itself
 };
 
 // The filter w [cout][cin][ks][ks] in bf16 and in the order the bf16 kernel
@@ -274,10 +275,12 @@ bool conv3x3_bf16_stride2(Ctx &cx, View in, const float *scale_shift, const uint
 bool conv3x3_bf16(Ctx &cx, View in, const float *scale_shift, const uint16_t *wq, int ci, int co, Geo g,
                   Epilogue ep, const View *r, View out, float *scratch);
 
-// How conv3x3_bf16 forms a result, where it takes the layer: input channels of a chunk (0: not taken), and in how many
-// parts, each a launch's own sum, they are split; and the chunk of the general kernel (0: no tiling).
+// How conv3x3_bf16 forms a result, where it takes the layer: input channels of a chunk (0: not taken), in how many parts, each
+// a launch's own sum, they are split, and whether the launch that adds the parts leaves statistics of 64-pixel tiles;
+// and the chunk of the general kernel (0: no tiling).
 struct Conv3x3Bf16Form {
     int chunk, parts;
+    bool sum_emits;
 };
 Conv3x3Bf16Form conv3x3_bf16_form(int ci, int co, const Geo &g);
 int conv_bf16_chunk(int ci, int co, int ks, const Geo &g);

@@ -42,6 +42,8 @@ SAME_BITS = [
     # (images, channels, rows, columns); blocks that are whole, so that both kernels leave statistics
     (33, 16, 32, 32), (24, 16, 8, 8), (140, 16, 32, 32), (33, 32, 16, 16), (300, 32, 16, 16), (40, 48, 16, 16), (20, 40, 32, 32),
     (64, 56, 8, 8), (33, 64, 16, 16), (20, 64, 32, 32),
+    # blocks that are not whole, in layers that the wider kernel splits and leaves statistics of
+    (20, 64, 24, 24), (17, 56, 40, 40), (30, 64, 16, 12), (25, 56, 32, 6), (70, 56, 4, 48),
     # ragged, where the general kernel's chunks are 16, 32 and 64 channels: with a filter that the driver converts
     (20, 44, 13, 11), (20, 46, 14, 30), (17, 56, 7, 6), (17, 64, 5, 2), (30, 52, 20, 21), (60, 61, 12, 12),
     # and without
