@@ -83,21 +83,6 @@ int class_of(int ci, int co) {
     return most <= 16 ? 16 : most <= 32 ? 32 : most <= 64 ? 64 : 0;
 }
 
-// Where the line lies (forward pass of two basic blocks, us, kernels before / this one; beyond the line with 16x16 tiles):
-//  * 33 to 64 channels: a block reads the whole filter (73 KB from L2) for 128 pixels at most, and the register-tiled kernel
-//    for 256 as soon as it has enough blocks not to split the channels.  64 channels: 32 of 32x32 242 / 148, 8 of 56x56 221 /
-//    177; beyond, 10 of 56x56 177 / 215, 128 of 32x32 256 / 374.  A filter that is converted here costs twice the reads:
-//    44 channels, 13 of 27x23 133 / 102; 60, 64 of 13x13 141 / 126; beyond, 36, 8 of 40x40 163 / 174, 33, 64 of 16x16 163 / 166.
-//  * 17 to 32 channels in rows that are not whole quads: 28 channels, 51 of 19x21 122 / 100, 26, 128 of 20x20 (whole quads) 129 /
-//    111; beyond, 32, 128 of 31x31 165 / 170, 28, 64 of 55x55 231 / 237.  In rows of whole quads there is no such
-//    size: 32 channels, 128 of 56x56 404 / 369.
-//  * up to 16 channels: 0.59 to 0.96 over 16 shapes from four images of 2x2 to 64 of 112x112.
-bool takes(int cls, bool converted, const Geo &g) {
-    if (cls == 64) return g.pixels() <= (converted ? 32768 : 11264);
-    if (cls == 32) return g.w % 4 == 0 || g.pixels() <= 65536;
-    return cls == 16;
-}
-
 struct C3nLaunch {
     C3nArgs a;
     int cls, nt, passes, order;  // cls: 16, 32 or 64 channels
@@ -105,6 +90,29 @@ struct C3nLaunch {
     dim3 grid;
     size_t lds_bytes;
 };
+
+// Where the line lies (forward pass of two basic blocks, time over that of the kernels before):
+//  * 33 to 64 channels: a block reads the whole filter (73 KB from L2) for 64 or 128 pixels, so what counts is whether the
+//    blocks run side by side, one on each of the 256 compute units: 0.41 to 0.95 over 106 shapes up to there.  A second
+//    block per unit: 40 to 56 channels up to 512 blocks and 32768 pixels 0.65 to 1.02 over 50 shapes, 588 blocks of 44 channels
+//    1.04; 60 to 64 channels 1.01 to 1.19.  Where conv3x3_bf16 splits the channels and needs a second launch for their sum
+//    (49 to 64, whole octets, at most 128 of its blocks) 0.52 to 1.00 at up to 720 blocks.
+//    A filter that is converted here costs twice the reads and conversions (33 to 42 channels, not whole octets): blocks of 64 pixels,
+//    at most 256 of them, 0.48 to 0.94 over 45 shapes; 288 to 320 1.07 to 1.15, blocks of 128 pixels from 128 on 1.01
+//    to 1.22; rows that need such blocks (more than 64 pixels): 64 blocks 0.82, 128 1.06.
+//  * 17 to 32 channels in rows that are not whole quads: 0.42 to 1.02 over 49 shapes up to 65536 pixels, 0.99 to 1.11 from
+//    79000 on; 32 channels, one chunk of the register-tiled kernel, 0.75 to 1.00 at up to 20 images of 30x34, 1.02 at 51072
+//    and 1.05 at 62208 pixels.  In rows of whole quads 0.75 to 1.02 up to 128 images of 56x56.
+//  * up to 16 channels: 0.59 to 0.99 over 48 shapes from four images of 2x2 to 64 of 112x112.
+bool takes(const C3nLaunch &L, const C3nPlan &pl, const Conv3x3Bf16Form &form, bool converted, int ci, int co, const Geo &g) {
+    if (L.cls == 64) {
+        if (!converted) return pl.blocks <= (L.nt == 1 ? 256 : 64);
+        if (form.parts > 1) return true;
+        return pl.blocks <= 256 || (std::max(ci, co) <= 56 && pl.blocks <= 512 && g.pixels() <= 32768);
+    }
+    if (L.cls == 32) return g.w % 4 == 0 || g.pixels() <= (ci == 32 ? 49152 : 65536);
+    return true;
+}
 
 template <int NT, int CH, int PASSES, int ORDER, bool W32 = false, bool GEN_ONLY = false>
 void launch_order(Ctx &cx, const C3nLaunch &L) {
@@ -150,19 +158,21 @@ void launch_c3n(Ctx &cx, const C3nLaunch &L) {
 bool plan_launch(View in, const float *scale_shift, const float *w, const uint16_t *wq, int ci, int co, Geo g, Epilogue ep,
                  const View *r, View out, C3nLaunch &L) {
     L.cls = class_of(ci, co);
-    if (!takes(L.cls, wq != nullptr, g)) return false;
+    if (L.cls == 0) return false;
     const int wp = 4 / chan_waves(L.cls);
     C3nPlan pl{};
-    // The larger block if it still gives every compute unit one (where the filter is converted in the kernel, every
-    // second one).
+    // The larger block if it still gives every compute unit one (up to 32 channels with a filter that is converted in the
+    // kernel, every second one).
     for (int nt = 2; nt >= 1; --nt) {
         const C3nPlan next = plan_c3n(g, 8 * nt * wp, L.cls);
         if (next.passes == 0) continue;
         pl = next;
         L.nt = nt;
-        if (pl.blocks >= (wq ? 256 : 128)) break;
+        if (pl.blocks >= (wq || L.cls == 64 ? 256 : 128)) break;
     }
     if (pl.passes == 0) return false;
+    const Conv3x3Bf16Form form = L.cls > 16 ? conv3x3_bf16_form(ci, co, g) : Conv3x3Bf16Form{16, 1, false};
+    if (!takes(L, pl, form, wq != nullptr, ci, co, g)) return false;
     // bytes from the base to the end of the last plane; every one must end below kNowhere
     const int64_t in_b = 4 * ((g.n - 1) * in.sn + (ci - 1) * in.sc + g.hw()), out_b = 4 * ((g.n - 1) * out.sn + (co - 1) * out.sc + g.hw());
     const int64_t r_b = r ? 4 * ((g.n - 1) * r->sn + (co - 1) * r->sc + g.hw()) : 0;
@@ -179,8 +189,8 @@ bool plan_launch(View in, const float *scale_shift, const float *w, const uint16
     L.gen = g.w % 4 != 0 || ci % 8 != 0 || (!wq && L.cls != 16);
     L.whole = g.w % 4 == 0 && pl.s.quads == 8 * L.nt * wp && g.n % pl.s.IMGS == 0 && g.h % pl.s.TH == 0;
     L.passes = pl.passes;
-    const Conv3x3Bf16Form form = conv3x3_bf16_form(ci, co, g);
-    if (wq && form.chunk > 0) L.order = form.parts > 1 ? kHalves : form.chunk / 16;
+    if (L.cls == 16) L.order = kChunk16;
+    else if (wq && form.chunk > 0) L.order = form.parts > 1 ? kHalves : form.chunk / 16;
     else L.order = std::max(16, conv_bf16_chunk(ci, co, 3, g)) / 16;
     L.owes = wq && form.sum_emits && !(L.whole && !L.gen);
     // (64-channel class: no caller has these, see launch_c3n)

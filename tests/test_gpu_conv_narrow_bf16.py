@@ -1,13 +1,45 @@
 """bf16 3x3 layers of up to 64 channels, at the sizes where the pixel blocks, staging passes, channel octets and channel
 classes of their kernels end, against the oracle with operands rounded to bf16; the check, its bars and the infinities
 next to the tensors are those of the ragged-channel layers."""
+import ctypes
+
 import numpy as np
 import pytest
 
 import synth_inputs as S
 import test_gpu_ragged_channels as R
 
-pytestmark = pytest.mark.gpu
+
+def form(c, n, h, w, converted):
+    """(class, tiles per wavefront, passes, ragged, order, whole blocks) of a layer of c channels; None: another kernel."""
+    import paper_1707_04585_amd as rv
+    query = rv.load_library().rvn_conv3x3_bf16_narrow_form
+    query.restype = ctypes.c_int64
+    v = query(c, c, n, h, w, int(converted))
+    return None if v < 0 else tuple(v >> 8 * k & 255 for k in range(5, -1, -1))
+
+
+# (channels, images, rows, columns, filter converted by the driver, taken): shapes that were timed on both kernels
+LINE = [
+    # one block per compute unit, and two
+    (60, 64, 13, 13, 1, 1), (60, 100, 13, 13, 1, 0), (60, 30, 27, 23, 1, 0), (44, 100, 13, 13, 1, 1), (44, 42, 27, 23, 1, 0),
+    (48, 14, 40, 40, 1, 0), (48, 48, 14, 14, 1, 1), (52, 50, 19, 21, 1, 1),
+    # the register-tiled kernel splits, and does not
+    (64, 9, 56, 56, 1, 1), (64, 10, 56, 56, 1, 0), (64, 32, 28, 28, 1, 1), (64, 33, 28, 28, 1, 0), (64, 128, 14, 14, 1, 1),
+    (64, 140, 14, 14, 1, 0), (64, 32, 32, 32, 1, 1), (64, 40, 32, 32, 1, 0),
+    # a filter converted in the kernel
+    (36, 64, 13, 13, 0, 1), (33, 80, 13, 13, 0, 0), (42, 21, 12, 50, 0, 1), (36, 32, 19, 21, 0, 0), (33, 8, 8, 70, 0, 1), (33, 16, 8, 70, 0, 0),
+    # ragged rows of up to 32 channels
+    (28, 64, 31, 31, 0, 1), (28, 100, 31, 31, 0, 0), (32, 100, 19, 21, 1, 1), (32, 128, 19, 21, 1, 0), (32, 200, 20, 20, 1, 1),
+]
+
+
+@pytest.mark.parametrize("shape", LINE, ids=lambda k: "c%d n%d %dx%d-%d" % k[:5])
+def test_line(shape):
+    """The kernel takes a layer where it was the faster one."""
+    *layer, converted, taken = shape
+    assert (form(*layer, converted) is not None) == bool(taken)
+
 
 CASES = [
     # up to 16 channels: two taps an instruction
@@ -33,6 +65,7 @@ CASES = [
 ]
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("case", CASES, ids=lambda k: "n%d c%d %dx%d" % (k["n"], k["c"], k["h"], k["w"]))
 def test_block(case):
     R.test_block(dict(kind="basic", **case))
@@ -51,6 +84,7 @@ SAME_BITS = [
 ]
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("shape", SAME_BITS, ids=lambda k: "n%d c%d %dx%d" % k)
 def test_forward_bits_are_those_of_the_wider_kernels(shape):
     """Sums and statistics keep the order of the kernels that take the layer where this one does not: tensors that end just
