@@ -15,7 +15,7 @@
 //  * input channels past the last one are skipped four at a time.
 // Measured, forward launch of 16 -> 16 channels with statistics: 128 images of 32x32 15.8 -> 12.0 us; 8 -> 8 at 4 of 8x8
 // (one workgroup) 11.4 -> 4.7 us.  28 -> 28 at 19x21, 51 images (flat-pixel kernel before): 14.7 -> 11.8 us, data
-// gradient 9.5.
+// gradient 9.5 (beside the filter gradient it has a kernel of its own, conv3x3_f32_bwd.hip).
 #include <algorithm>
 
 #include "conv3x3_f32_body.h"
@@ -36,10 +36,30 @@ __global__ __launch_bounds__(kThreads, 2) void conv3x3_f32_k(const C3fArgs p) {
 // Multiplier of fdiv_c3f: exact for e * d < 2^32 (e is a thread or block index here).
 uint32_t mul_of(int d) { return d == 1 ? 0u : (uint32_t)((1ull << 32) / (uint64_t)d + 1ull); }
 
-// Up to 32 output channels.  Training steps of two basic blocks against the kernels before (row-band, flat-pixel for
-// rows that are not whole quads): 0.43 to 0.86 of the time for 31 shapes of up to 32 channels, 1.00 to 1.02 for two of
-// 28 to 30.  From 33 channels on the flat-pixel kernel's 32-row tiles win: 33 to 64 channels took 0.87 to 1.45.
-bool takes(int co) { return co <= 32; }
+// Up to 32 output channels.  Against the row-band kernel 0.31 to 0.86 of the time (forward of two basic blocks).  From 33
+// channels on the flat-pixel kernel's 32-row tiles win: 33 to 64 channels took 0.87 to 1.45.
+// Where the flat-pixel kernel takes the layer too (17 to 32 channels, rows that are not whole quads) both run in rounds
+// over the 256 compute units: this one by its blocks of 64 quads, which rows and images fill to 60 to 95 %, that one by
+// pixels, so each is ahead just where the other has begun another round, by a fifth to a half.
+//  * up to 128 blocks: 0.77 to 1.03.  At 32 channels, a whole number of that kernel's chunks, that begins at 16384
+//    pixels (1.04 to 1.17 below); in rows of more than 32 pixels at 4096 (1.00 to 1.18 below, with three rows staged for one).
+//  * above, a round of 256 blocks takes as long as two of 32768 pixels: with channels that leave a part of that kernel's
+//    last chunk empty 0.66 to 1.01 where the even number is rounded up, with whole octets 0.85 to 1.00 where it is rounded
+//    down, up to four rounds, and no gain beyond.  One round more 1.02 to 1.50.
+//  * its 64-pixel tiles with chunks of 16 channels take nearly twice as long per round: 0.79 to 0.96.
+//  * rows of 64 pixels and more, where it stages twice its tile: 0.60 to 1.02.
+// Measured over 1152 shapes of 2000 to 400000 pixels; none that this rule sends here takes more than 1.04.
+bool takes(int ci, int co, const Geo &g, const C3fPlan &pl) {
+    if (co > 32) return false;
+    const ConvGemmTile flat = conv_gemm_f32_tile(ci, co, 3, g);
+    if (flat.pixels == 0) return true;
+    const int64_t px = g.pixels();
+    if (g.w >= 64) return px >= 4096;
+    if (pl.blocks <= 128) return ci >= 32 ? px > 16384 : px >= 4096 || g.w <= 32;
+    const bool slow = flat.pixels == 64 && flat.chunk == 16, octets = ci % 8 == 0;
+    const int64_t rounds = (pl.blocks + 255) / 256, single = (px + 32767) / 32768, theirs = slow ? 2 * single - 1 : single;
+    return theirs > 1 && 2 * rounds <= theirs + (octets ? 0 : 1) && (!octets || slow || theirs <= 4);
+}
 
 template <bool TR>
 void launch_c3f(Ctx &cx, const C3fLaunch &L) {
@@ -96,9 +116,9 @@ C3fPlan plan_c3f(const Geo &g, int waves) {
 
 bool conv3x3_f32_plan(View in, const float *scale_shift, const float *w, bool transposed, int ci, int co, Geo g,
                       Epilogue ep, const View *r, View out, C3fLaunch &L) {
-    if (!takes(co)) return false;
+    if (co > 32) return false;
     const C3fPlan pl = plan_c3f(g, 4);
-    if (pl.passes == 0) return false;
+    if (pl.passes == 0 || !takes(ci, co, g, pl)) return false;
     // bytes from the base to the end of the last plane; every one must end below kNowhere
     const int64_t in_b = 4 * ((g.n - 1) * in.sn + (ci - 1) * in.sc + g.hw()), out_b = 4 * ((g.n - 1) * out.sn + (co - 1) * out.sc + g.hw());
     const int64_t r_b = r ? 4 * ((g.n - 1) * r->sn + (co - 1) * r->sc + g.hw()) : 0, w_b = (int64_t)ci * co * 36;
@@ -123,6 +143,16 @@ bool conv3x3_f32_plan(View in, const float *scale_shift, const float *w, bool tr
     L.grid = dim3((unsigned)pl.blocks, (unsigned)((co + L.mt * 16 - 1) / (L.mt * 16)));
     L.lds_bytes = (size_t)pl.passes * pl.s.cpp * pl.s.plane * 4;
     return true;
+}
+
+// How a layer of dense, aligned tensors runs, for the tests: channel tiles of a workgroup, staging passes, whole quads a row, whole
+// blocks (statistics are left of the output), in pairs of hexadecimal digits, or -1 (another kernel).
+extern "C" int rvn_conv3x3_f32_form(int ci, int co, int n, int h, int w) {
+    const Geo g{n, h, w};
+    float *const at = reinterpret_cast<float *>(256);
+    C3fLaunch L;
+    if (!conv3x3_f32_plan(dense_view(at, ci, g), at, at, false, ci, co, g, EP_STORE, nullptr, dense_view(at, co, g), L)) return -1;
+    return ((L.mt * 256 + L.passes) * 256 + (int)L.vec) * 256 + (int)(L.vec && L.whole);
 }
 
 bool conv3x3_f32(Ctx &cx, View in, const float *scale_shift, const float *w, bool transposed, int ci, int co, Geo g,

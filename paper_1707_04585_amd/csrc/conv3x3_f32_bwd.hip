@@ -212,6 +212,16 @@ __global__ __launch_bounds__(64 * NW, 2) void conv3x3_f32_bwd_k(const B3fArgs p)
     }
 }
 
+// Where the flat-pixel kernels take both gradients too (17 to 32 channels, rows that are not whole quads; two launches): as
+// long as a workgroup has one block this kernel is ahead, 0.77 to 0.97 of the time of a training step of two basic blocks; from
+// there on both run in rounds, this one of `upw` blocks a workgroup, those of 32768 pixels.  Two rounds against three, three
+// against five, four against six, five against eight 0.85 to 0.99; with fewer in hand 0.93 to 1.11, most above 1 (426 shapes
+// of 3000 to 255000 pixels).
+bool takes(int cin, int cout, const Geo &g, int upw) {
+    if (upw == 1 || conv_gemm_f32_tile(cout, cin, 3, g).pixels == 0) return true;
+    return 3 * upw <= 2 * ((g.pixels() + 32767) / 32768);
+}
+
 struct B3fLaunch {
     B3fArgs a;
     WgradReduce red;
@@ -251,6 +261,7 @@ bool plan_b3f(View x, const float *scale_shift, View dh, const float *w, int cin
     if (slices < 1) return false;
     a.units = (int)pl.blocks;
     a.upw = (int)((pl.blocks + slices - 1) / slices);
+    if (!takes(cin, cout, g, a.upw)) return false;
     slices = (pl.blocks + a.upw - 1) / a.upw;
     a.d_lds = pl.passes * pl.s.cpp * pl.s.plane;
     L.a = a;
@@ -301,6 +312,18 @@ void launch_b3f(Ctx &cx, const B3fLaunch &L, int parts) {
 }
 
 }  // namespace
+
+// How the gradients of a layer of dense, aligned tensors run, for the tests: wavefronts, staging passes, chunks of output
+// channels, whole quads a row, in pairs of hexadecimal digits, or -1 (kernels of their own).
+extern "C" int rvn_conv3x3_f32_bwd_form(int cin, int cout, int n, int h, int w) {
+    const Geo g{n, h, w};
+    float *const at = reinterpret_cast<float *>(256);
+    B3fLaunch L;
+    if (!wgrad_rows_fit(cin, cout, 3, g) ||
+        !plan_b3f(dense_view(at, cin, g), at, dense_view(at, cout, g), at, cin, cout, g, at, wgrad_scratch_floats(cin, cout, 3, g), at, false, at, L))
+        return -1;
+    return ((L.waves * 256 + L.passes) * 256 + (cout > 16 ? 2 : 1)) * 256 + (int)L.vec;
+}
 
 bool separate_launches() {
     const char *e = std::getenv("RVN_SEPARATE_LAUNCHES");

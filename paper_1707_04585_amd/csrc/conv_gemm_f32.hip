@@ -375,6 +375,11 @@ bool takes(int co, const Geo &g) { return co > 32 || (co > 16 && (g.w & 3) != 0)
 
 }  // namespace
 
+ConvGemmTile conv_gemm_f32_tile(int ci, int co, int ks, const Geo &g) {
+    const int shape = takes(co, g) ? choose_shape(g, ci, co, ks) : -1;
+    return shape < 0 ? ConvGemmTile{0, 0} : ConvGemmTile{kShapes[shape].bn(), kShapes[shape].kc};
+}
+
 // Which instance a layer of dense tensors runs on (3x3 layers of up to 32 channels: where conv3x3_f32 does not take
 // them), for the tests: shape * 4096 + pieces * 512 + pitch, or -1 (another kernel).
 extern "C" int rvn_conv_gemm_f32_instance(int ci, int co, int ks, int n, int h, int w) {

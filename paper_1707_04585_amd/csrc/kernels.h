@@ -245,6 +245,11 @@ void conv_fwd(Ctx &cx, View x, const float *scale_shift, rvn_dtype dt, const flo
 
 // The same convolution with fp32 operands as a tiled matrix product over the flat pixel index
 // (conv_gemm_f32.hip); returns false (nothing launched) for the shapes it does not take.
+// The pixels of its tile and the channels of its chunk for such a layer, whatever the extents; 0: not taken.
+struct ConvGemmTile {
+    int pixels, chunk;
+};
+ConvGemmTile conv_gemm_f32_tile(int ci, int co, int ks, const Geo &g);
 bool conv_gemm_f32(Ctx &cx, View in, const float *scale_shift, const float *w, bool transposed, int ci, int co, int ks,
                    Geo g, Epilogue ep, const View *r, View out);
 

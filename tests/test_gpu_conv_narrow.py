@@ -4,8 +4,6 @@ import pytest
 
 import test_gpu_conv_gemm as G
 
-pytestmark = pytest.mark.gpu
-
 CASES = [
     # one pixel an image (not with one channel: the BN layer behind it removes its scale, and with it the gradient)
     dict(n=40, c=10, h=1, w=1),
@@ -14,15 +12,15 @@ CASES = [
     dict(n=4, c=16, h=8, w=8),         # one block, whole
     dict(n=5, c=32, h=8, w=8),         # a last block of one image; 16 channels
     dict(n=2, c=32, h=9, w=32),        # a last band of one row
-    dict(n=3, c=26, h=7, w=65),        # 17 quads a row, 8 staging passes, ragged
-    dict(n=2, c=18, h=6, w=64),        # 16 quads a row, 8 staging passes
+    dict(n=3, c=26, h=7, w=65),        # 17 quads a row, ragged
+    dict(n=2, c=18, h=6, w=64),        # 16 quads a row
     dict(n=2, c=32, h=4, w=160),       # widest rows with a backward plan
     dict(n=2, c=34, h=3, w=166),       # nearly the widest rows taken; forward only
     dict(n=1, c=34, h=2, w=172),       # too wide: row-band kernel; forward only
     dict(n=6, c=34, h=11, w=13),       # a second channel tile of one channel, a second chunk of one
     dict(n=3, c=64, h=16, w=16),       # two full channel tiles, whole blocks
-    dict(n=130, c=34, h=32, w=15),     # 256 blocks and more: both channel tiles in one workgroup; ragged
-    dict(n=64, c=40, h=16, w=64),      # the same with 8 staging passes, rows of whole quads
+    dict(n=130, c=34, h=32, w=15),     # the flat-pixel kernel's by its rounds; the gradients not
+    dict(n=64, c=40, h=16, w=64),      # 256 blocks and more: both channel tiles in one workgroup; whole blocks, 8 staging passes
     dict(n=86, c=36, h=9, w=66),       # the same, ragged
     dict(n=128, c=64, h=16, w=32),     # the same, whole blocks
 ]
@@ -33,6 +31,40 @@ WIDER = [
 ]
 
 
+# (channels, images, rows, columns, forward taken, gradients taken): ragged layers that were timed on both kernels
+LINE = [
+    (18, 58, 19, 21, 1, 1), (18, 72, 19, 21, 0, 1), (18, 85, 19, 21, 1, 1), (24, 142, 13, 13, 0, 1), (24, 210, 13, 13, 1, 1),
+    (24, 285, 13, 13, 0, 0), (28, 20, 41, 41, 1, 1), (28, 57, 41, 41, 0, 1), (28, 1858, 9, 9, 1, 0), (28, 946, 13, 13, 1, 0),
+    (32, 31, 19, 21, 0, 1), (32, 47, 19, 21, 1, 1), (32, 138, 33, 35, 0, 0), (32, 86, 31, 31, 1, 1), (32, 182, 31, 31, 0, 1),
+    # rows whose gradients are refused
+    (32, 40, 4, 150, 1, 0), (17, 4, 6, 101, 0, 0), (17, 20, 6, 101, 1, 0),
+    # channels that the flat-pixel kernels do not take
+    (16, 946, 13, 13, 1, 1),
+]
+
+
+def forward(c, n, h, w):
+    """(channel tiles, staging passes, whole quads, whole blocks) of the forward launch; None: another kernel."""
+    import paper_1707_04585_amd as rv
+    v = rv.load_library().rvn_conv3x3_f32_form(c, c, n, h, w)
+    return None if v < 0 else tuple(v >> 8 * k & 255 for k in (3, 2, 1, 0))
+
+
+def gradients(c, n, h, w):
+    """(wavefronts, staging passes, chunks of output channels, whole quads) of the gradient launch; None: other kernels."""
+    import paper_1707_04585_amd as rv
+    v = rv.load_library().rvn_conv3x3_f32_bwd_form(c, c, n, h, w)
+    return None if v < 0 else tuple(v >> 8 * k & 255 for k in (3, 2, 1, 0))
+
+
+@pytest.mark.parametrize("shape", LINE, ids=lambda k: "c%d n%d %dx%d" % k[:4])
+def test_line(shape):
+    """A layer that the flat-pixel kernels take as well goes to the faster ones."""
+    *layer, fwd, bwd = shape
+    assert (forward(*layer) is not None, gradients(*layer) is not None) == (bool(fwd), bool(bwd))
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("case", CASES + WIDER, ids=lambda k: "n%d c%d %dx%d" % (k["n"], k["c"], k["h"], k["w"]))
 def test_block_against_oracle(case, monkeypatch):
     if case["c"] <= 32:  # (the filter gradient's limit on the row length is twice that of wider layers)
