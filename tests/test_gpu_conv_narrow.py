@@ -1,5 +1,8 @@
 """fp32 3x3 layers of up to 32 channels, at the sizes where the pixel blocks, staging passes and channel tiles of
-their kernels end, against the oracle in float64 (the check and its bars are those of the flat-pixel kernels)."""
+their kernels end, against the oracle in float64 (the check and its bars are those of the flat-pixel kernels).  Every
+compiled instance of the forward and of the gradient kernel is launched by a case; a host test sees to that."""
+import random
+
 import pytest
 
 import test_gpu_conv_gemm as G
@@ -23,6 +26,16 @@ CASES = [
     dict(n=64, c=40, h=16, w=64),      # 256 blocks and more: both channel tiles in one workgroup; whole blocks, 8 staging passes
     dict(n=86, c=36, h=9, w=66),       # the same, ragged
     dict(n=128, c=64, h=16, w=32),     # the same, whole blocks
+    # the other instances: forward
+    dict(n=8, c=12, h=4, w=8),         # one tile, 8 passes, whole blocks
+    dict(n=270, c=36, h=5, w=28),      # both tiles, blocks that are not whole
+    dict(n=283, c=38, h=1, w=114),     # both tiles, 8 passes, ragged
+    dict(n=18, c=34, h=16, w=136),     # both tiles, 8 passes, blocks that are not whole
+    # and gradients: four wavefronts, 8 passes
+    dict(n=11, c=20, h=1, w=11), dict(n=16, c=34, h=1, w=6), dict(n=4, c=36, h=1, w=32),
+    # eight wavefronts
+    dict(n=132, c=10, h=93, w=1), dict(n=134, c=10, h=4, w=68), dict(n=141, c=36, h=37, w=1),
+    dict(n=382, c=10, h=1, w=85), dict(n=3, c=10, h=88, w=156), dict(n=310, c=34, h=1, w=62), dict(n=152, c=38, h=4, w=40),
 ]
 # flat-pixel instances that the cases of their own test reach through layers of up to 32 channels
 WIDER = [
@@ -55,6 +68,24 @@ def gradients(c, n, h, w):
     import paper_1707_04585_amd as rv
     v = rv.load_library().rvn_conv3x3_f32_bwd_form(c, c, n, h, w)
     return None if v < 0 else tuple(v >> 8 * k & 255 for k in (3, 2, 1, 0))
+
+
+def test_every_instance_has_a_case():
+    """Every instance that a large sample of layers selects is launched by a case above."""
+    layers = [(k["c"] // 2, k["n"], k["h"], k["w"]) for k in CASES]
+    have, have_b = {forward(*l) for l in layers}, {gradients(*l) for l in layers}
+    rng = random.Random(5)
+    log = lambda lo, hi: int(round(lo * (hi / lo) ** rng.random()))
+    seen, seen_b = set(), set()
+    for _ in range(40000):
+        layer = (rng.randint(1, 32), log(1, 512), log(1, 128), log(1, 180))
+        for c, n, h, w in (layer, (layer[0], layer[1], 4 * (layer[2] // 4) or 1, 4 * (layer[3] // 4) or 4)):
+            if n * h * w <= 1000000:
+                seen.add(forward(c, n, h, w))
+                seen_b.add(gradients(c, n, h, w))
+    assert len(seen - {None}) == 12 and len(seen_b - {None}) == 16
+    assert seen - {None} <= have, seen - have
+    assert seen_b - {None} <= have_b, seen_b - have_b
 
 
 @pytest.mark.parametrize("shape", LINE, ids=lambda k: "c%d n%d %dx%d" % k[:4])
