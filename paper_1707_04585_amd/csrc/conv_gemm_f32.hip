@@ -367,8 +367,8 @@ bool launch_shape(Ctx &cx, const GemmArgs &a, int shape, Plane pl, dim3 grid) {
 }
 
 // Fewer than 17 channels would leave half of a 32-row tile idle; above, this kernel took a quarter to a half of the
-// row-band kernel's time.  3x3 layers of up to 32 channels go to conv3x3_f32 first; what comes here has rows too long
-// for it.  1x1 layers of up to 32 channels have neither advantage and stay there only because the line was drawn for
+// row-band kernel's time.  3x3 layers of up to 32 channels go to conv3x3_f32 first; what comes here is
+// what its own rule leaves, and rows too long for it.  1x1 layers of up to 32 channels have neither advantage and stay there only because the line was drawn for
 // 3x3: with them and their filter gradients here, two bottleneck blocks of 64 channels reduced to 32 take 884 us
 // instead of 1196 (8 images of 28x28), of 128 to 32 2136 instead of 2302 (32 of 56x56), and no shape tried took longer.
 bool takes(int co, const Geo &g) { return co > 32 || (co > 16 && (g.w & 3) != 0); }
@@ -380,10 +380,13 @@ ConvGemmTile conv_gemm_f32_tile(int ci, int co, int ks, const Geo &g) {
     return shape < 0 ? ConvGemmTile{0, 0} : ConvGemmTile{kShapes[shape].bn(), kShapes[shape].kc};
 }
 
-// Which instance a layer of dense tensors runs on (3x3 layers of up to 32 channels: where conv3x3_f32 does not take
-// them), for the tests: shape * 4096 + pieces * 512 + pitch, or -1 (another kernel).
+extern "C" int rvn_conv3x3_f32_form(int ci, int co, int n, int h, int w);
+
+// Which instance a layer of dense tensors runs on, for the tests: shape * 4096 + pieces * 512 + pitch, or -1 (another
+// kernel, conv3x3_f32 among them).
 extern "C" int rvn_conv_gemm_f32_instance(int ci, int co, int ks, int n, int h, int w) {
     const Geo g{n, h, w};
+    if (ks == 3 && rvn_conv3x3_f32_form(ci, co, n, h, w) >= 0) return -1;
     const int shape = takes(co, g) ? choose_shape(g, ci, co, ks) : -1;
     if (shape < 0) return -1;
     const Plane pl = plane_of(kShapes[shape], w);

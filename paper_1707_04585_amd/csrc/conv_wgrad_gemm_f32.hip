@@ -265,9 +265,13 @@ void run_one(Ctx &cx, const WgemmArgs &a) {
 
 }  // namespace
 
-// Which instance a layer runs on given the scratch it is planned with, for the tests: ks * 8 + pieces (3x3) or tile shape (1x1), or -1.
+extern "C" int rvn_conv3x3_f32_bwd_form(int cin, int cout, int n, int h, int w);
+
+// Which instance a layer of dense tensors runs on given the scratch it is planned with, for the tests: ks * 8 + pieces (3x3) or
+// tile shape (1x1), or -1 (another kernel, that of both gradients among them).
 extern "C" int rvn_conv_wgrad_gemm_f32_instance(int cin, int cout, int ks, int n, int h, int w) {
     const Geo g{n, h, w};
+    if (ks == 3 && rvn_conv3x3_f32_bwd_form(cin, cout, n, h, w) >= 0) return -1;
     const WgemmPlan p = plan(cin, cout, ks, g, wgrad_scratch_floats(cin, cout, ks, g));
     return p.ok ? ks * 8 + (ks == 3 ? p.seg : p.shape) : -1;
 }

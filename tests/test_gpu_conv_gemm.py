@@ -16,7 +16,7 @@ from oracle import revnet_oracle as O
 
 # (most leave a remainder of pixels and of channels in every tile)
 CASES = [
-    dict(kind="basic", n=3, c=34, h=3, w=7),        # 17 channels, the fewest taken; 63 pixels
+    dict(kind="basic", n=3, c=34, h=3, w=7),        # 17 channels, 63 pixels (conv3x3_f32, as some of the next)
     dict(kind="basic", n=1, c=66, h=5, w=13),       # 33 channels, 65 pixels
     dict(kind="basic", n=1, c=66, h=7, w=9),        # 63 pixels
     dict(kind="basic", n=1, c=70, h=2, w=63),       # widest rows of the 128-pixel pitch; 35 channels
@@ -34,14 +34,19 @@ CASES = [
     # the remaining tile shapes (channels x pixels) of the 3x3 kernel, by 8- and 16-channel chunks
     dict(kind="basic", n=40, c=66, h=41, w=10),     # 64 x 128
     dict(kind="basic", n=5, c=66, h=53, w=31),      # 64 x 64
-    dict(kind="basic", n=80, c=34, h=5, w=41),      # 32 x 128
-    dict(kind="basic", n=95, c=34, h=30, w=23),     # 32 x 64, 8-channel chunks
-    dict(kind="basic", n=99, c=34, h=17, w=39),     # the same with the wider pitch
+    dict(kind="basic", n=80, c=34, h=5, w=41),      # (conv3x3_f32)
+    dict(kind="basic", n=95, c=34, h=30, w=23),     # (conv3x3_f32)
+    dict(kind="basic", n=99, c=34, h=17, w=39),     # (conv3x3_f32)
     dict(kind="basic", n=19, c=66, h=36, w=12),     # 32 x 128, 16-channel chunks
-    dict(kind="basic", n=20, c=34, h=10, w=41),     # 32 x 64, 16-channel chunks, four pieces
+    dict(kind="basic", n=20, c=34, h=10, w=41),     # (conv3x3_f32)
     dict(kind="basic", n=101, c=130, h=9, w=12),    # 32 x 32, one piece
     dict(kind="basic", n=1, c=34, h=2, w=34),       # 32 x 32, two pieces
     dict(kind="basic", n=1, c=34, h=2, w=49),       # 32 x 32, four pieces
+    dict(kind="basic", n=22, c=130, h=12, w=32),    # 32 x 128, 8-channel chunks
+    dict(kind="basic", n=6, c=130, h=19, w=72),     # 32 x 64, 8-channel chunks, the wider pitch
+    dict(kind="basic", n=10, c=66, h=10, w=42),     # 32 x 64, 16-channel chunks, four pieces
+    dict(kind="basic", n=1, c=66, h=1, w=35),       # 32 x 32, two pieces
+    dict(kind="basic", n=1, c=66, h=1, w=48),       # 32 x 32, four pieces
     # and of the 1x1 kernel
     dict(kind="bottleneck", n=5, c=818, h=49, w=19, width=17),    # 64 x 64
     dict(kind="bottleneck", n=24, c=38, h=53, w=26, width=17),    # 32 x 128
