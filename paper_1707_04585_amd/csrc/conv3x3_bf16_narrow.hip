@@ -114,22 +114,31 @@ bool takes(const C3nLaunch &L, const C3nPlan &pl, const Conv3x3Bf16Form &form, b
     return true;
 }
 
+// What no plan leads to is not compiled: tiles of 32 pixels by twos mean at least 512 partial results, beyond what
+// conv3x3_bf16_narrow_merges allows (a filter converted here allows them from half the blocks on); from 17 channels on a whole
+// block of theirs is more than one staging pass.
 template <int NT, int CH, int PASSES, int ORDER, bool W32 = false, bool GEN_ONLY = false>
 void launch_order(Ctx &cx, const C3nLaunch &L) {
+    constexpr bool kMerges = PASSES == 1 && (NT == 1 || W32), kEmits = !(NT == 2 && PASSES == 1 && CH > 16);
 #define RVN_RUN(G_, E_, M_) cx.run(conv3x3_bf16_narrow_k<NT, CH, PASSES, G_, E_, W32, ORDER, M_>, L.grid, dim3(kThreads), L.lds_bytes, L.a)
     if constexpr (GEN_ONLY) {
         RVN_RUN(true, false, false);
     } else {
-        if constexpr (PASSES == 1) {
-            if (L.a.merge.blocks > 0) {
+        if (L.a.merge.blocks > 0) {
+            if constexpr (kMerges) {
                 if (L.a.emit) RVN_RUN(false, true, true);
                 else RVN_RUN(false, false, true);
-                return;
+            } else {
+                cx.fail(hipErrorInvalidConfiguration);
             }
+        } else if (L.gen) {
+            RVN_RUN(true, false, false);
+        } else if (L.a.emit) {
+            if constexpr (kEmits) RVN_RUN(false, true, false);
+            else cx.fail(hipErrorInvalidConfiguration);
+        } else {
+            RVN_RUN(false, false, false);
         }
-        if (L.gen) RVN_RUN(true, false, false);
-        else if (L.a.emit) RVN_RUN(false, true, false);
-        else RVN_RUN(false, false, false);
     }
 #undef RVN_RUN
 }
@@ -203,16 +212,18 @@ bool plan_launch(View in, const float *scale_shift, const float *w, const uint16
 }  // namespace
 
 // How a layer of dense tensors runs, for the tests: class (16, 32 or 64 channels), 32-pixel tiles a wavefront has, staging passes,
-// whether the rows or channels are ragged, Order, whether every block is whole; in hexadecimal digits pairs from the
-// class down, or -1 (another kernel).
+// whether the rows or channels are ragged, Order, whether every block is whole, whether the filter comes converted; in pairs of
+// hexadecimal digits from the class down, or -1 (another kernel).  converted: -1 for what the driver does in a function of two
+// such layers.
 extern "C" int64_t rvn_conv3x3_bf16_narrow_form(int ci, int co, int n, int h, int w, int converted) {
     const Geo g{n, h, w};
+    if (converted < 0) converted = (int64_t)ci * co * 9 >= 16384 || conv3x3_bf16_ok(ci, co, g);
     const uint16_t wq = 0;
     float f = 0.f;
     C3nLaunch L;
     if (!plan_launch(dense_view(&f, ci, g), &f, &f, converted ? &wq : nullptr, ci, co, g, EP_STORE, nullptr, dense_view(&f, co, g), L)) return -1;
     int64_t form = 0;
-    for (int v : {L.cls, L.nt, L.passes, (int)L.gen, L.order, (int)L.whole}) form = form * 256 + v;
+    for (int v : {L.cls, L.nt, L.passes, (int)L.gen, L.order, (int)(L.whole && !L.gen), converted}) form = form * 256 + v;
     return form;
 }
 
@@ -235,7 +246,7 @@ bool conv3x3_bf16_narrow_unconverted(const Ctx &cx, int ci, int co, Geo g, const
 bool conv3x3_bf16_narrow_takes(View in, const float *scale_shift, const float *w, const uint16_t *wq, int ci, int co, Geo g,
                                Epilogue ep, const View *r, View out) {
     C3nLaunch L;
-    return plan_launch(in, scale_shift, w, wq, ci, co, g, ep, r, out, L) && L.passes == 1 && !L.gen;
+    return plan_launch(in, scale_shift, w, wq, ci, co, g, ep, r, out, L) && L.passes == 1 && !L.gen && (L.nt == 1 || !wq);
 }
 
 bool conv3x3_bf16_narrow(Ctx &cx, View in, const float *scale_shift, const float *w, const uint16_t *wq, int ci, int co, Geo g, Epilogue ep,
@@ -260,12 +271,12 @@ bool conv3x3_bf16_narrow(Ctx &cx, View in, const float *scale_shift, const float
         // statistics pass, so that the layers behind see the same bits.
         cx.emitted = EmittedStats{out.p, out.sn, out.sc, co, g.n, g.h, g.w, tiles, 64, nullptr, true};
     }
-#define RVN_CASE(NT_, CH_)                                                \
-    if (L.cls == CH_ && L.nt == NT_) {                                    \
-        if (L.passes == 1) launch_c3n<NT_, CH_, 1>(cx, L);                \
-        else launch_c3n<NT_, CH_, 2>(cx, L);                              \
-    }
-    RVN_CASE(1, 16) RVN_CASE(2, 16) RVN_CASE(1, 32) RVN_CASE(2, 32) RVN_CASE(1, 64) RVN_CASE(2, 64)
+#define RVN_CASE(NT_, CH_, P_) \
+    if (L.cls == CH_ && L.nt == NT_ && L.passes == P_) launch_c3n<NT_, CH_, P_>(cx, L);
+    // (one tile of up to 16 channels is at most 192 staging items: one pass)
+    RVN_CASE(1, 16, 1) RVN_CASE(2, 16, 1) RVN_CASE(2, 16, 2)
+    RVN_CASE(1, 32, 1) RVN_CASE(1, 32, 2) RVN_CASE(2, 32, 1) RVN_CASE(2, 32, 2)
+    RVN_CASE(1, 64, 1) RVN_CASE(1, 64, 2) RVN_CASE(2, 64, 1) RVN_CASE(2, 64, 2)
 #undef RVN_CASE
     return true;
 }
