@@ -154,24 +154,10 @@ C3Plan plan_c3(int ci, int co, const Geo &g, int stride = 1) {
 // Whether the wavefronts of the kernel that sums a split layer are whole runs of 64 pixels of one plane.
 bool sum_emits(int co, const Geo &g) { return g.hw() % 64 == 0 && g.pixels() * co % kThreads == 0; }
 
-// More than 64 KB of dynamic LDS has to be asked for, once per kernel.
-template <typename K>
-bool raise_lds_limit(Ctx &cx, K kernel, bool &raised) {
-    if (raised || cx.dry) return true;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
-    if (e != hipSuccess) {
-        cx.fail(e);
-        return false;
-    }
-    raised = true;
-    return true;
-}
-
 template <int WM, int MTW, int NTW, int KC, bool EMIT, int NI, bool RAGGED>
 void launch_c3_items(Ctx &cx, const C3Launch &L, dim3 grid) {
-    static bool raised = false;
-    if (!raise_lds_limit(cx, conv3x3_bf16_k<WM, MTW, NTW, KC, EMIT, NI, RAGGED>, raised)) return;
+    static OncePerDevice raised;
+    if (!raise_lds_limit(cx, conv3x3_bf16_k<WM, MTW, NTW, KC, EMIT, NI, RAGGED>, L.lds_bytes, 80 * 1024, raised)) return;
     cx.run(conv3x3_bf16_k<WM, MTW, NTW, KC, EMIT, NI, RAGGED>, grid, dim3(kThreads), L.lds_bytes, L.a);
 }
 

@@ -281,16 +281,8 @@ bool plan_b3f(View x, const float *scale_shift, View dh, const float *w, int cin
 
 template <int NW, int PASSES, int KT, bool VEC>
 void run_one(Ctx &cx, const B3fLaunch &L, const B3fArgs &a) {
-    static bool raised = false;  // more than 64 KB of LDS has to be asked for, once per kernel
-    if (!raised && !cx.dry) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(conv3x3_f32_bwd_k<NW, PASSES, KT, VEC>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e != hipSuccess) {
-            cx.fail(e);
-            return;
-        }
-        raised = true;
-    }
+    static OncePerDevice raised;
+    if (!raise_lds_limit(cx, conv3x3_f32_bwd_k<NW, PASSES, KT, VEC>, L.lds_bytes, 160 * 1024, raised)) return;
     // While the chip has room the two gradients get workgroups of their own: half the chain of one that does both.
     dim3 grid = L.grid;
     if (a.parts == (kDgrad | kWgrad) && grid.x * grid.y <= 128) grid.z = 2;

@@ -85,19 +85,10 @@ __global__ __launch_bounds__(kThreads, 2) void dgrad3_bf16_wgrad16_k(const C3Arg
     }
 }
 
-// More than 64 KB of dynamic LDS has to be asked for, once per kernel.
 template <typename K, typename A, typename B>
-bool launch_pair(Ctx &cx, K kernel, bool &raised, unsigned blocks, size_t lds, const A &c, const B &w,
+bool launch_pair(Ctx &cx, K kernel, OncePerDevice &raised, unsigned blocks, size_t lds, const A &c, const B &w,
                  const PairGrid &q) {
-    if (!raised && !cx.dry && lds > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
-        if (e != hipSuccess) {
-            cx.fail(e);
-            return false;
-        }
-        raised = true;
-    }
+    if (!raise_lds_limit(cx, kernel, lds, 80 * 1024, raised)) return false;
     cx.run(kernel, dim3(blocks), dim3(kThreads), lds, c, w, q);
     return true;
 }
@@ -106,7 +97,7 @@ template <int MTW, int KC, int NI, bool VEC, bool DH16>
 void launch3(Ctx &cx, const C3Launch &C, const WgLaunch &W, const PairGrid &q, unsigned blocks, size_t lds) {
 #define RVN_CASE(MT_, CT_)                                                                                          \
     if (W.MT == MT_ && W.CT == CT_) {                                                                               \
-        static bool raised = false;                                                                                 \
+        static OncePerDevice raised;                                                                                \
         launch_pair(cx, dgrad_wgrad3_bf16_k<MTW, KC, NI, MT_, CT_, VEC, DH16>, raised, blocks, lds, C.a, W.a, q);        \
     }
     RVN_CASE(1, 1) RVN_CASE(1, 2) RVN_CASE(2, 1) RVN_CASE(2, 2)
@@ -117,7 +108,7 @@ template <int MTW, int DEPTH, bool GEN, bool VEC, bool DH16>
 void launch1(Ctx &cx, const C1Launch &C, const WgLaunch &W, const PairGrid &q, unsigned blocks, size_t lds) {
 #define RVN_CASE(MT_, CT_)                                                                                          \
     if (W.MT == MT_ && W.CT == CT_) {                                                                               \
-        static bool raised = false;                                                                                 \
+        static OncePerDevice raised;                                                                                \
         launch_pair(cx, dgrad_wgrad1_bf16_k<MTW, DEPTH, GEN, MT_, CT_, VEC, DH16>, raised, blocks, lds, C.a, W.a, q);    \
     }
     RVN_CASE(1, 1) RVN_CASE(1, 2) RVN_CASE(2, 1) RVN_CASE(2, 2)
@@ -154,7 +145,7 @@ bool pair_small(Ctx &cx, View x, const float *scale_shift, View dh, const uint16
     cx.cost.conv_flops += 2.0 * flops;
     *defer = red;
     if (cx.launch(K_CONV_DGRAD_WGRAD, 2.0 * (P * cin * 4.0 + P * cout * 4.0), 2.0 * flops)) {
-        static bool raised[2] = {false, false};
+        static OncePerDevice raised[2];
         if (C.NI == 1) launch_pair(cx, dgrad3_bf16_wgrad16_k<1>, raised[0], (unsigned)blocks, lds, C.a, W.a, q);
         else launch_pair(cx, dgrad3_bf16_wgrad16_k<c3::kInItems>, raised[1], (unsigned)blocks, lds, C.a, W.a, q);
     }

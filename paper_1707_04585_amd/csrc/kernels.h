@@ -6,6 +6,7 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 
+#include "once_per_device.h"
 #include "revnet.h"
 
 namespace rvn {
@@ -176,6 +177,21 @@ struct Ctx {
         if (err == hipSuccess) err = e;
     }
 };
+
+// More than 64 KB of dynamic LDS has to be asked for, once per kernel and device; most: what any launch of the kernel needs.
+// False: that failed, which cx records.
+template <typename K>
+bool raise_lds_limit(Ctx &cx, K kernel, size_t bytes, int most, OncePerDevice &raised) {
+    if (cx.dry || bytes <= 64 * 1024) return true;
+    int device = 0;
+    hipError_t e = hipGetDevice(&device);
+    if (e == hipSuccess && raised.wanted(device)) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, most);
+        if (e == hipSuccess) raised.made(device);
+    }
+    if (e != hipSuccess) cx.fail(e);
+    return e == hipSuccess;
+}
 
 // The second half of a filter gradient: the ordered sum of its partial results.
 // conv_wgrad either launches it or hands it to the caller, who lets another

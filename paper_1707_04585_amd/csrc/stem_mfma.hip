@@ -226,16 +226,8 @@ template <int MT>
 bool launch_fwd(Ctx &cx, View x, const float *w, const StemShape &g, View out) {
     StemTiling tl;
     if (!stem_tiling(g, MT, &tl)) return false;
-    static bool raised = false;  // more than 64 KB of dynamic LDS has to be asked for once
-    if (!raised) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(stem_conv_mfma_k<MT>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBudget);
-        if (e != hipSuccess) {
-            cx.fail(e);
-            return true;
-        }
-        raised = true;
-    }
+    static OncePerDevice raised;
+    if (!raise_lds_limit(cx, stem_conv_mfma_k<MT>, tl.lds_bytes, (int)kLdsBudget, raised)) return true;
     const dim3 grid((unsigned)(g.N * tl.bands), (unsigned)((g.CO + 16 * MT - 1) / (16 * MT)));
     cx.run(stem_conv_mfma_k<MT>, grid, dim3(kThreads), tl.lds_bytes, (const float *)x.p, x.sn, x.sc, w, out.p, out.sn,
            out.sc, g, tl);
@@ -393,16 +385,8 @@ __global__ __launch_bounds__(kThreads) void stem_wgrad_mfma_k(const float *__res
 
 template <int NTW>
 void launch_wgrad(Ctx &cx, View x, View dh, const StemShape &g, const StemWgradTiling &tl, float *part) {
-    static bool raised = false;
-    if (!raised) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(stem_wgrad_mfma_k<NTW>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBudget);
-        if (e != hipSuccess) {
-            cx.fail(e);
-            return;
-        }
-        raised = true;
-    }
+    static OncePerDevice raised;
+    if (!raise_lds_limit(cx, stem_wgrad_mfma_k<NTW>, tl.lds_bytes, (int)kLdsBudget, raised)) return;
     const dim3 grid((unsigned)tl.chunks, (unsigned)((g.CO + 63) / 64));
     cx.run(stem_wgrad_mfma_k<NTW>, grid, dim3(kThreads), tl.lds_bytes, (const float *)x.p, x.sn, x.sc,
            (const float *)dh.p, dh.sn, dh.sc, part, g, tl);

@@ -285,3 +285,28 @@ def test_static_workspace_entry_point_validates_and_rejects_oversize_on_the_host
     assert status_of(rv.revnet_stack_fwd_static, d, 0, x1, x2, [fake_params(d)], x1, x2)[0] == -2
     assert status_of(rv.revnet_stack_fwd_static, d, 1, x1, x1, [fake_params(d)], x1, x2)[0] == -6
     assert status_of(rv.revnet_stack_fwd_static, d, 1, big(0), x2, [fake_params(d)], x1, x2)[0] == -1
+
+
+def test_a_setting_made_on_one_device_is_still_wanted_on_the_next(tmp_path):
+    """The limit on a kernel's dynamic LDS is asked for once per device of the process, whichever thread comes first."""
+    import subprocess
+    src = tmp_path / "once.cpp"
+    src.write_text("""
+#include <thread>
+#include <vector>
+#include "once_per_device.h"
+int main() {
+    static rvn::OncePerDevice once;
+    auto make = [](int device) { if (once.wanted(device)) once.made(device); };
+    std::vector<std::thread> threads;
+    for (int t = 0; t < 8; ++t) threads.emplace_back([=] { for (int d = 0; d < 63; d += 2) make(d); });
+    for (auto &t : threads) t.join();
+    for (int d = 0; d < 64; ++d)
+        if (once.wanted(d) != (d % 2 == 1)) return 1;
+    make(64);
+    return once.wanted(64) && once.wanted(1000) && once.wanted(-1) ? 0 : 2;
+}
+""")
+    exe = tmp_path / "once"
+    subprocess.run(["g++", "-std=c++17", "-pthread", "-I", os.path.join(ROOT, "paper_1707_04585_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    subprocess.run([str(exe)], check=True)
