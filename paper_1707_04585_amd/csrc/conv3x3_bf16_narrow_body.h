@@ -207,8 +207,9 @@ __device__ __forceinline__ double shfl_xor_f64(double v, int mask) {
 }
 
 // The merge of bn_stats_merge_k by one workgroup for all of its channels: 256 / CH neighbouring lanes share a channel.  Equal
-// counts, so means are averaged (about the first one) instead of merged pair by pair; all in double.  Scale
-// and shift go to `ss` [2][CH].
+// counts, so means are averaged (about the first one) instead of merged pair by pair; all in double, so the floats that
+// come of it are those of the other form unless they lie within some 1e-15 of a rounding boundary.  Scale and shift
+// go to `ss` [2][CH].
 template <int CH>
 __device__ __forceinline__ void merge_statistics(const StatsMerge &m, float *ss, int tid, bool store) {
     constexpr int T = kThreads / CH;

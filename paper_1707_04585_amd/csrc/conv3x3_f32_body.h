@@ -1,5 +1,6 @@
 // Kernel body and argument block of the fp32 3x3 convolution of narrow layers (see conv3x3_f32.hip for the
-// design), as a device function so that a launch can hold it next to another body.  Device code only.
+// design); its staging, filter and operand helpers also serve the kernel of both gradients (conv3x3_f32_bwd.hip) and, the
+// buffer accesses, the bf16 form.  Device code only, but for the plans.
 #pragma once
 
 #include "kernels.h"
@@ -77,8 +78,9 @@ __device__ __forceinline__ f4_t load4(__amdgpu_buffer_rsrc_t b, uint32_t lane, u
     return *reinterpret_cast<const f4_t *>(&v);
 }
 // The whole offset in the lane part.  With a register as the scalar offset the compiler takes a store of more
-// than 8 bytes to need no wait state before its data registers are written again; on this chip it does: beside
-// the other body of the shared gradient launch such stores wrote what came into the registers next.
+// than 8 bytes to need no wait state before its data registers are written again; on this chip it does: in a kernel
+// where other instructions followed at once (a launch of this body and a filter gradient's, since given up) such
+// stores wrote what came into the registers next.
 __device__ __forceinline__ void store4(__amdgpu_buffer_rsrc_t b, uint32_t lane, f4_t v) {
     __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u4_t *>(&v), b, lane, 0, 0);
 }
