@@ -83,12 +83,11 @@ int class_of(int ci, int co) {
     return most <= 16 ? 16 : most <= 32 ? 32 : most <= 64 ? 64 : 0;
 }
 
-struct C3nLaunch {
-    C3nArgs a;
-    int cls, nt, passes, order;  // cls: 16, 32 or 64 channels
-    bool gen, whole, owes;       // owes: leaves no statistics where conv3x3_bf16 would
-    dim3 grid;
-    size_t lds_bytes;
+// What depends on the sizes of a layer alone.
+struct C3nChoice {
+    bool converted, taken, sum_emits;
+    int cls, nt, order;  // class of channels (16, 32 or 64), 32-pixel tiles of a wavefront, Order
+    C3nPlan pl;
 };
 
 // Where the line lies (forward pass of two basic blocks, time over that of the kernels before):
@@ -97,22 +96,55 @@ struct C3nLaunch {
 //    block per unit: 40 to 56 channels up to 512 blocks and 32768 pixels 0.65 to 1.02 over 50 shapes, 588 blocks of 44 channels
 //    1.04; 60 to 64 channels 1.01 to 1.19.  Where conv3x3_bf16 splits the channels and needs a second launch for their sum
 //    (49 to 64, whole octets, at most 128 of its blocks) 0.52 to 1.00 at up to 720 blocks.
-//    A filter that is converted here costs twice the reads and conversions (33 to 42 channels, not whole octets): blocks of 64 pixels,
-//    at most 256 of them, 0.48 to 0.94 over 45 shapes; 288 to 320 1.07 to 1.15, blocks of 128 pixels from 128 on 1.01
-//    to 1.22; rows that need such blocks (more than 64 pixels): 64 blocks 0.82, 128 1.06.
-//  * 17 to 32 channels in rows that are not whole quads: 0.42 to 1.02 over 49 shapes up to 65536 pixels, 0.99 to 1.11 from
-//    79000 on; 32 channels, one chunk of the register-tiled kernel, 0.75 to 1.00 at up to 20 images of 30x34, 1.02 at 51072
-//    and 1.05 at 62208 pixels.  In rows of whole quads 0.75 to 1.02 up to 128 images of 56x56.
+//    A filter that is converted here (33 to 42 channels, not whole octets), a chunk of 16 or 32 channels at a time: up to 512
+//    blocks of 64 pixels 0.48 to 0.97 over 190 shapes, 588 1.02 to 1.17; up to 336 blocks of 128 pixels 0.61 to 0.96.  In
+//    chunks of 64, all of it in registers beforehand: up to 256 blocks of 64 pixels 0.40 to 0.93, beyond and with
+//    blocks of 128 1.02 to 1.19.
+//  * 17 to 32 channels in rows that are not whole quads: 0.42 to 1.04 over 130 shapes up to 65536 pixels, 0.99 to 1.11 from
+//    79000 on; with 25 and more channels in rows of more than 32 pixels, and with 32, one chunk of the register-tiled kernel,
+//    0.75 to 1.00 up to 49152 pixels and 0.98 to 1.09 above.  In rows of whole quads 0.75 to 1.02 up to 128 images of 56x56.
 //  * up to 16 channels: 0.59 to 0.99 over 48 shapes from four images of 2x2 to 64 of 112x112.
-bool takes(const C3nLaunch &L, const C3nPlan &pl, const Conv3x3Bf16Form &form, bool converted, int ci, int co, const Geo &g) {
-    if (L.cls == 64) {
-        if (!converted) return pl.blocks <= (L.nt == 1 ? 256 : 64);
+bool takes(const C3nChoice &c, const Conv3x3Bf16Form &form, int ci, int co, const Geo &g) {
+    if (c.cls == 64) {
+        if (!c.converted) return c.order == kChunk64 ? c.nt == 1 && c.pl.blocks <= 256 : c.pl.blocks <= (c.nt == 1 ? 512 : 336);
         if (form.parts > 1) return true;
-        return pl.blocks <= 256 || (std::max(ci, co) <= 56 && pl.blocks <= 512 && g.pixels() <= 32768);
+        return c.pl.blocks <= 256 || (std::max(ci, co) <= 56 && c.pl.blocks <= 512 && g.pixels() <= 32768);
     }
-    if (L.cls == 32) return g.w % 4 == 0 || g.pixels() <= (ci == 32 ? 49152 : 65536);
+    if (c.cls == 32) return g.w % 4 == 0 || g.pixels() <= (ci == 32 || (g.w > 32 && std::max(ci, co) > 24) ? 49152 : 65536);
     return true;
 }
+
+C3nChoice choose(int ci, int co, const Geo &g, bool converted) {
+    C3nChoice c{};
+    c.converted = converted;
+    c.cls = class_of(ci, co);
+    if (c.cls == 0) return c;
+    // The larger block if it still gives every compute unit one (up to 32 channels with a filter that is converted in the
+    // kernel, every second one).
+    for (int nt = 2; nt >= 1; --nt) {
+        const C3nPlan next = plan_c3n(g, 8 * nt * (4 / chan_waves(c.cls)), c.cls);
+        if (next.passes == 0) continue;
+        c.pl = next;
+        c.nt = nt;
+        if (next.blocks >= (converted || c.cls == 64 ? 256 : 128)) break;
+    }
+    if (c.pl.passes == 0) return c;
+    const Conv3x3Bf16Form form = c.cls > 16 ? conv3x3_bf16_form(ci, co, g) : Conv3x3Bf16Form{16, 1, false};
+    if (c.cls == 16) c.order = kChunk16;
+    else if (converted && form.chunk > 0) c.order = form.parts > 1 ? kHalves : form.chunk / 16;
+    else c.order = std::max(16, conv_bf16_chunk(ci, co, 3, g)) / 16;
+    c.sum_emits = form.sum_emits;
+    c.taken = takes(c, form, ci, co, g);
+    return c;
+}
+
+struct C3nLaunch {
+    C3nArgs a;
+    int cls, nt, passes, order;  // cls: 16, 32 or 64 channels
+    bool gen, whole, owes;       // owes: leaves no statistics where conv3x3_bf16 would
+    dim3 grid;
+    size_t lds_bytes;
+};
 
 // What no plan leads to is not compiled: tiles of 32 pixels by twos mean at least 512 partial results, beyond what
 // conv3x3_bf16_narrow_merges allows (a filter converted here allows them from half the blocks on); from 17 channels on a whole
@@ -166,22 +198,10 @@ void launch_c3n(Ctx &cx, const C3nLaunch &L) {
 
 bool plan_launch(View in, const float *scale_shift, const float *w, const uint16_t *wq, int ci, int co, Geo g, Epilogue ep,
                  const View *r, View out, C3nLaunch &L) {
-    L.cls = class_of(ci, co);
-    if (L.cls == 0) return false;
-    const int wp = 4 / chan_waves(L.cls);
-    C3nPlan pl{};
-    // The larger block if it still gives every compute unit one (up to 32 channels with a filter that is converted in the
-    // kernel, every second one).
-    for (int nt = 2; nt >= 1; --nt) {
-        const C3nPlan next = plan_c3n(g, 8 * nt * wp, L.cls);
-        if (next.passes == 0) continue;
-        pl = next;
-        L.nt = nt;
-        if (pl.blocks >= (wq || L.cls == 64 ? 256 : 128)) break;
-    }
-    if (pl.passes == 0) return false;
-    const Conv3x3Bf16Form form = L.cls > 16 ? conv3x3_bf16_form(ci, co, g) : Conv3x3Bf16Form{16, 1, false};
-    if (!takes(L, pl, form, wq != nullptr, ci, co, g)) return false;
+    const C3nChoice c = choose(ci, co, g, wq != nullptr);
+    if (!c.taken) return false;
+    const C3nPlan &pl = c.pl;
+    L.cls = c.cls; L.nt = c.nt; L.order = c.order;
     // bytes from the base to the end of the last plane; every one must end below kNowhere
     const int64_t in_b = 4 * ((g.n - 1) * in.sn + (ci - 1) * in.sc + g.hw()), out_b = 4 * ((g.n - 1) * out.sn + (co - 1) * out.sc + g.hw());
     const int64_t r_b = r ? 4 * ((g.n - 1) * r->sn + (co - 1) * r->sc + g.hw()) : 0;
@@ -196,12 +216,9 @@ bool plan_launch(View in, const float *scale_shift, const float *w, const uint16
     a.s = pl.s;
     L.a = a;
     L.gen = g.w % 4 != 0 || ci % 8 != 0 || (!wq && L.cls != 16);
-    L.whole = g.w % 4 == 0 && pl.s.quads == 8 * L.nt * wp && g.n % pl.s.IMGS == 0 && g.h % pl.s.TH == 0;
+    L.whole = g.w % 4 == 0 && pl.s.quads == 8 * L.nt * (4 / chan_waves(L.cls)) && g.n % pl.s.IMGS == 0 && g.h % pl.s.TH == 0;
     L.passes = pl.passes;
-    if (L.cls == 16) L.order = kChunk16;
-    else if (wq && form.chunk > 0) L.order = form.parts > 1 ? kHalves : form.chunk / 16;
-    else L.order = std::max(16, conv_bf16_chunk(ci, co, 3, g)) / 16;
-    L.owes = wq && form.sum_emits && !(L.whole && !L.gen);
+    L.owes = wq && c.sum_emits && !(L.whole && !L.gen);
     // (64-channel class: no caller has these, see launch_c3n)
     if (L.cls > 16 && !L.gen && (L.order == kChunk64 || (L.cls == 64 && L.order == kChunk32))) return false;
     L.grid = dim3((unsigned)pl.blocks);

@@ -320,20 +320,32 @@ __device__ __forceinline__ void conv3x3_bf16_narrow_body(const C3nArgs &p, int b
 
     if (MERGE) __syncthreads();  // scale and shift are there
     st.commit(s, lds, ss_lds, bn);
+    constexpr int CS = ORDER == kHalves ? 1 : ORDER;  // 16-channel steps of a chunk
+    // Steps of the filter that are there before the first is used: all, or a chunk where 64 channels have to be converted
+    // (the next step's 72 fp32 taps beside the operands of all four spilled 84 to 116 registers: forward of three blocks
+    // of 34 channels, 12 images of 28x28, 200 us, now 158).
+    constexpr int AHEAD = W32 && CH == 64 ? CS : KS;
 #pragma unroll
-    for (int ks = KS1; ks < KS; ++ks) load_filter<W32>(w_rs, p, ko, ks, kg, w[ks]);
+    for (int ks = KS1; ks < AHEAD; ++ks) load_filter<W32>(w_rs, p, ko, ks, kg, w[ks]);
     __syncthreads();
     const int row_bytes = s.pitch * REC;
 #pragma unroll
-    for (int i = 0; i < 9 * KS; ++i) {
-        constexpr int CS = ORDER == kHalves ? 1 : ORDER;  // 16-channel steps of a chunk
-        const int chunk = i / (9 * CS), tap = i % (9 * CS) / CS, ks = chunk * CS + i % CS;
-        const int h = ORDER == kHalves && ks >= 2 ? 1 : 0;
-        bf16x8_t a[NT];
+    for (int c0 = 0; c0 < KS; c0 += CS) {
+        if (AHEAD < KS && c0 > 0) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t) a[t] = *reinterpret_cast<const bf16x8_t *>(win[t] + tap / 3 * row_bytes + (tap % 3 * REC + ks * 32));
+            for (int ks = c0; ks < c0 + CS; ++ks) load_filter<W32>(w_rs, p, ko, ks, kg, w[ks]);
+        }
+        const int h = ORDER == kHalves && c0 >= 2 ? 1 : 0;
 #pragma unroll
-        for (int t = 0; t < NT; ++t) acc[h][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t], w[ks][tap], acc[h][t], 0, 0, 0);
+        for (int tap = 0; tap < 9; ++tap)
+#pragma unroll
+            for (int ks = c0; ks < c0 + CS; ++ks) {
+                bf16x8_t a[NT];
+#pragma unroll
+                for (int t = 0; t < NT; ++t) a[t] = *reinterpret_cast<const bf16x8_t *>(win[t] + tap / 3 * row_bytes + (tap % 3 * REC + ks * 32));
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[h][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t], w[ks][tap], acc[h][t], 0, 0, 0);
+            }
     }
     if constexpr (ORDER == kHalves) {
 #pragma unroll

@@ -31,10 +31,12 @@ LINE = [
     # the register-tiled kernel splits, and does not
     (64, 9, 56, 56, 1, 1), (64, 10, 56, 56, 1, 0), (64, 32, 28, 28, 1, 1), (64, 33, 28, 28, 1, 0), (64, 128, 14, 14, 1, 1),
     (64, 140, 14, 14, 1, 0), (64, 32, 32, 32, 1, 1), (64, 40, 32, 32, 1, 0),
-    # a filter converted in the kernel
-    (36, 64, 13, 13, 0, 1), (33, 80, 13, 13, 0, 0), (42, 21, 12, 50, 0, 1), (36, 32, 19, 21, 0, 0), (33, 8, 8, 70, 0, 1), (33, 16, 8, 70, 0, 0),
+    # a filter converted in the kernel, a chunk of channels at a time and all at once
+    (36, 100, 16, 16, 0, 1), (42, 42, 27, 23, 0, 0), (36, 33, 12, 50, 0, 1), (33, 33, 8, 70, 0, 1), (33, 50, 8, 70, 0, 0),
+    (36, 64, 13, 13, 0, 1), (33, 80, 13, 13, 0, 0), (36, 32, 19, 21, 0, 0), (39, 64, 19, 21, 0, 0),
     # ragged rows of up to 32 channels
-    (28, 64, 31, 31, 0, 1), (28, 100, 31, 31, 0, 0), (32, 100, 19, 21, 1, 1), (32, 128, 19, 21, 1, 0), (32, 200, 20, 20, 1, 1),
+    (28, 64, 31, 31, 0, 1), (28, 100, 31, 31, 0, 0), (28, 45, 31, 33, 0, 1), (28, 50, 31, 33, 0, 0), (22, 63, 31, 33, 0, 1),
+    (32, 100, 19, 21, 1, 1), (32, 128, 19, 21, 1, 0), (32, 200, 20, 20, 1, 1),
 ]
 
 
@@ -80,7 +82,7 @@ INSTANCES = [
     (2, 56, 4, 44), (1, 56, 4, 64), (1, 40, 5, 52), (1, 40, 4, 64), (2, 56, 3, 43), (2, 33, 4, 44), (2, 40, 3, 43), (1, 33, 4, 64),
     (2, 43, 3, 48), (348, 37, 1, 1), (288, 44, 1, 1),
     (128, 56, 12, 12), (143, 40, 34, 4), (141, 56, 18, 5), (133, 33, 40, 4), (345, 45, 17, 1), (149, 44, 17, 6),
-    (1, 40, 4, 68), (128, 40, 4, 64), (1, 56, 4, 82), (1, 33, 13, 66), (1, 40, 4, 66), (1, 33, 4, 68), (1, 43, 4, 72), (64, 44, 16, 24),
+    (1, 40, 4, 68), (128, 40, 4, 64), (1, 56, 4, 82), (1, 33, 13, 66), (1, 40, 4, 66), (1, 33, 4, 68), (1, 43, 4, 72), (64, 44, 16, 24), (279, 33, 20, 1),
 ]
 WIDEST_BACKWARD = 168
 CASES += [dict(n=n, c=2 * c, h=h, w=w) for n, c, h, w in INSTANCES]
