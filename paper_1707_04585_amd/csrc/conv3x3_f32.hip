@@ -41,24 +41,26 @@ uint32_t mul_of(int d) { return d == 1 ? 0u : (uint32_t)((1ull << 32) / (uint64_
 // Where the flat-pixel kernel takes the layer too (17 to 32 channels, rows that are not whole quads) both run in rounds
 // over the 256 compute units: this one by its blocks of 64 quads, which rows and images fill to 60 to 95 %, that one by
 // pixels, so each is ahead just where the other has begun another round, by a fifth to a half.
-//  * up to 128 blocks: 0.77 to 1.03.  At 32 channels, a whole number of that kernel's chunks, that begins at 16384
-//    pixels (1.04 to 1.17 below); in rows of more than 32 pixels at 4096 (1.00 to 1.18 below, with three rows staged for one).
-//  * above, a round of 256 blocks takes as long as two of 32768 pixels: with channels that leave a part of that kernel's
-//    last chunk empty 0.66 to 1.01 where the even number is rounded up, with whole octets 0.85 to 1.00 where it is rounded
-//    down, up to four rounds, and no gain beyond.  One round more 1.02 to 1.50.
+//  * up to 128 blocks: 0.77 to 1.03.  In rows of up to 32 pixels that begins at 16384 pixels from 29 channels on (as many
+//    fours as 32; 1.02 to 1.10 below), in longer rows at 4096 (1.00 to 1.18 below, with three rows staged for one).
+//  * above, a round of 256 blocks takes as long as two of 32768 pixels.  This kernel multiplies channels in fours, that one in
+//    eights: with 17 to 20 and 25 to 28 channels 0.66 to 1.01 where the even number of rounds is rounded up, with 21 to 24 and 29
+//    to 32 0.85 to 1.00 where it is rounded down, up to four rounds (six where channels are not whole octets), and no gain
+//    beyond.  One round more 1.02 to 1.50.
 //  * its 64-pixel tiles with chunks of 16 channels take nearly twice as long per round: 0.79 to 0.96.
 //  * rows of 64 pixels and more, where it stages twice its tile: 0.60 to 1.02.
-// Measured over 1152 shapes of 2000 to 400000 pixels; none that this rule sends here takes more than 1.04.
+// Measured over 1362 shapes of 2000 to 400000 pixels; none that this rule sends here takes more than 1.04.
 bool takes(int ci, int co, const Geo &g, const C3fPlan &pl) {
     if (co > 32) return false;
     const ConvGemmTile flat = conv_gemm_f32_tile(ci, co, 3, g);
     if (flat.pixels == 0) return true;
     const int64_t px = g.pixels();
     if (g.w >= 64) return px >= 4096;
-    if (pl.blocks <= 128) return ci >= 32 ? px > 16384 : px >= 4096 || g.w <= 32;
-    const bool slow = flat.pixels == 64 && flat.chunk == 16, octets = ci % 8 == 0;
+    const int fours = (ci + 3) / 4;
+    if (pl.blocks <= 128) return g.w > 32 ? px >= 4096 : fours < 8 || px > 16384;
+    const bool slow = flat.pixels == 64 && flat.chunk == 16, octets = fours % 2 == 0;
     const int64_t rounds = (pl.blocks + 255) / 256, single = (px + 32767) / 32768, theirs = slow ? 2 * single - 1 : single;
-    return theirs > 1 && 2 * rounds <= theirs + (octets ? 0 : 1) && (!octets || slow || theirs <= 4);
+    return theirs > 1 && 2 * rounds <= theirs + (octets ? 0 : 1) && (!octets || slow || theirs <= (ci % 8 ? 6 : 4));
 }
 
 template <bool TR>

@@ -41,7 +41,7 @@ CASES = [
 LINE = [
     (18, 58, 19, 21, 1, 1), (18, 72, 19, 21, 0, 1), (18, 85, 19, 21, 1, 1), (24, 142, 13, 13, 0, 1), (24, 210, 13, 13, 1, 1),
     (24, 285, 13, 13, 0, 0), (28, 20, 41, 41, 1, 1), (28, 57, 41, 41, 0, 1), (28, 1858, 9, 9, 1, 0), (28, 946, 13, 13, 1, 0),
-    (32, 31, 19, 21, 0, 1), (32, 47, 19, 21, 1, 1), (32, 138, 33, 35, 0, 0), (32, 86, 31, 31, 1, 1), (32, 182, 31, 31, 0, 1),
+    (31, 4, 26, 23, 0, 1), (32, 31, 19, 21, 0, 1), (32, 47, 19, 21, 1, 1), (32, 138, 33, 35, 0, 0), (32, 86, 31, 31, 1, 1), (32, 182, 31, 31, 0, 1),
     # rows whose gradients are refused
     (32, 40, 4, 150, 1, 0), (17, 4, 6, 101, 0, 0), (17, 20, 6, 101, 1, 0),
     # channels that the flat-pixel kernels do not take
