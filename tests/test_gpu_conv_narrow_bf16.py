@@ -68,6 +68,8 @@ CASES = [
     dict(n=3, c=66, h=9, w=9),         # one channel into the third tile and the fifth octet
     dict(n=11, c=126, h=32, w=32),     # a last octet of seven channels
     dict(n=2, c=128, h=3, w=80),       # one row a block, two staging passes
+    # statistics by the pass in tiles: one workgroup a channel, and several
+    dict(n=2, c=128, h=8, w=24), dict(n=1, c=112, h=8, w=40), dict(n=6, c=128, h=24, w=24),
 ]
 # The remaining instances: (images, channels, rows, columns), by class, tiles per wavefront and staging passes.
 INSTANCES = [
@@ -124,6 +126,23 @@ def test_block(case):
     assert O.rel_l2(r.to_host(Y[0]), np.concatenate([y1, y2], 1)) < 1e-2
     with pytest.raises(rv.RevnetError):   # refused by the filter gradient
         r.backward(Y, Y, Y, Y)
+
+
+@pytest.mark.gpu
+def test_statistics_in_tiles_of_an_unaligned_tensor():
+    """The same pass where the stream's halves start one float off a 16-byte boundary."""
+    import torch
+    cfg = dict(kind="basic", n=3, c=128, h=8, w=24, width=None, depth=1, conv="bf16", affine="random")
+    x, params, dy = S.draw_stack(S.BASE_SEED + 1621, **cfg)
+
+    def halves(src, device):
+        out = []
+        for part in (src[:, :64], src[:, 64:]):
+            t = torch.empty(part.size + 1, dtype=torch.float32, device=device)[1:].view(part.shape)
+            out.append(t.copy_(torch.as_tensor(part.astype(np.float32))))
+        return out
+
+    R.check_block(cfg, x, params, dy, halves)
 
 
 SAME_BITS = [
